@@ -398,6 +398,30 @@ static hipError_t qr_bin(gmls_ctx ctx, const Options &o, int dim, int order, int
 // not depend on the call it came with.
 static bool fp64_fast(gmls_ctx ctx, int n) { return n >= kFp64FastMin && ctx->opt.qr_force < 0 && !ctx->timer; }
 
+// The QR kernel, in each bin's shape, on what the FP64 kernels of many targets
+// left of it in the set's queues (no cursor, rows of one bin being alike), and
+// on the whole long bin where `long_bin` (the wavefront kernel's calls).  200k
+// ill-conditioned 3-D targets, all of them left: order 2, 30 neighbours, 2720
+// us a call with one queue in the longest rows' shape, 1100 so (2450 by QR
+// alone); order 3, 40, 4290, 2200 and 2470; order 4, 100, 10600, 8500 and 5650
+// (the wavefront kernel sweeps a target before it knows).
+static hipError_t qr_left(gmls_ctx ctx, const Options &o, int dim, int order, int basis, const Pipe64Set &set,
+                          const int *list, const BinMeta *hm, BinMeta *meta, int n, bool long_bin, hipStream_t s) {
+  for (int b = 1; b < kNumBins; ++b) {
+    const int cnt = hm ? hm->count[b] : n;
+    if (cnt == 0) continue;
+    hipError_t e;
+    if (b == kLongBin && long_bin) {
+      e = qr_bin(ctx, o, dim, order, basis, b, cnt, set.a, nullptr, list, meta, s);
+    } else {
+      const QrShape q = kQrShapes[b][o.qr_shape[b]];
+      e = launch_qr_left(dim, order, basis, b, q.rpl, q.wpe, set, meta, std::min(cnt, ctx->cus * q.per_cu), s);
+    }
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // Buffers of the FP64 pipeline for windows of at most kPipe64Chunk targets
 // (GMLS_OPT_PIPE_CHUNK where that is less); get: false where they cannot be
 // had (capture-safe: were not grown by an earlier call), the call then takes
@@ -539,6 +563,7 @@ static gmls_status run_stencils(gmls_ctx ctx, const double *coords, int64_t n_sr
                                                           : (size_t)(F + (normals ? 1 : 0)) * Q,
                               n);
   const bool wave64 = fast && !normals && wave64_supported(dim, order, basis);
+  const Pipe64Set set{a, fb, meta->left[0]};
   if (prec == GMLS_PREC_MIXED && opt.scheme == MIXED_PIPE) {
     // moments [chunk][NM], solutions [chunk][F][Q] and records of one chunk of targets
     // (sized for every target, so that a capture-safe call finds the
@@ -557,14 +582,13 @@ static gmls_status run_stencils(gmls_ctx ctx, const double *coords, int64_t n_sr
       GMLS_HIP(launch_mixed_pipe(dim, order, mbasis, a, list, sync ? &hm : nullptr, meta, fb, stats, opt, mom, yb,
                                  rec, chunk, n, cus, ctx->timer, s));
   } else if (pipe64) {
-    const Pipe64Set set{a, fb, &meta->fb_count};
     const bool dv = basis == GMLS_BASIS_DIVFREE;
     if (!sync || hm.count[0] < n)
       GMLS_HIP(launch_fp64_pipe(dim, order, dv ? nullptr : &set, dv ? &set : nullptr, list, sync ? &hm : nullptr, meta,
                                 p64.mom, p64.coef, p64.sums, p64.rec, p64.chunk, n, cus, s));
   } else if (wave64) {
     if (!sync || hm.count[0] < n)
-      GMLS_HIP(launch_fp64_wave(dim, order, basis, a, list, sync ? &hm : nullptr, meta, fb, &meta->fb_count, n, cus, s));
+      GMLS_HIP(launch_fp64_wave(dim, order, basis, set, list, sync ? &hm : nullptr, meta, n, cus, s));
   } else if (prec == GMLS_PREC_MIXED && opt.scheme == MIXED_WAVE) {
     if (!sync || hm.count[0] < n)
       GMLS_HIP(launch_mixed_wave(dim, order, mbasis, a, list, sync ? &hm : nullptr, meta, fb, stats, opt, n, cus,
@@ -588,7 +612,7 @@ static gmls_status run_stencils(gmls_ctx ctx, const double *coords, int64_t n_sr
     af.ok_status = -1;  // keep the fallback/not-converged status set by the mixed kernel
     GMLS_HIP(launch_qr_fallback(dim, order, basis, af, fb, meta, 4, cus * 8, s));
   }
-  if (pipe64 || wave64) GMLS_HIP(launch_qr_fallback(dim, order, basis, a, fb, meta, 4, cus * 8, s));
+  if (pipe64 || wave64) GMLS_HIP(qr_left(ctx, opt, dim, order, basis, set, list, sync ? &hm : nullptr, meta, n, wave64, s));
   if (basis == GMLS_BASIS_DIVFREE)  // the queue is usually empty: a small persistent grid
     GMLS_HIP(launch_qr_kmat(dim, order, af, a.aux_list, &meta->aux_count, &meta->aux_cursor, 64, s));
   if (report) GMLS_HIP(hipEventRecord(ctx->ev[3], s));
@@ -703,27 +727,27 @@ static gmls_status run_shared(gmls_ctx ctx, const double *coords, int64_t n_src,
     // (pipeline) or a target's swept Gram (a wavefront per target for both)
     const BinMeta *hb = sync ? &hm : nullptr;
     const int qs = (int)binom_l(order + dim, dim);
-    const Pipe64Set p_s{as, fbs, &meta->fb_count}, p_v{av, fbv, &meta->fb2_count};
+    const Pipe64Set p_s{as, fbs, meta->left[0]}, p_v{av, fbv, meta->left[1]};
+    const bool ws = wave64_supported(dim, order, GMLS_BASIS_SCALAR);
     const bool pv = pipe64_supported(dim, order, GMLS_BASIS_DIVFREE);
     Fp64Pipe p64;
-    if (wave64_supported(dim, order, GMLS_BASIS_SCALAR)) {
-      GMLS_HIP(launch_fp64_wave_shared(dim, order, as, fbs, &meta->fb_count, av, fbv, &meta->fb2_count, list, hb, meta, n,
-                                       ctx->cus, s));
+    if (ws) {
+      GMLS_HIP(launch_fp64_wave_shared(dim, order, p_s, p_v, list, hb, meta, n, ctx->cus, s));
     } else if (p64.get(ctx, dim, order, std::max((size_t)Fs, pv ? (size_t)Fv * dim : 0) * qs, n)) {
       GMLS_HIP(launch_fp64_pipe(dim, order, &p_s, pv ? &p_v : nullptr, list, hb, meta, p64.mom, p64.coef, p64.sums,
                                 p64.rec, p64.chunk, n, ctx->cus, s));
       if (!pv)
-        GMLS_HIP(launch_fp64_wave(dim, order, GMLS_BASIS_DIVFREE, av, list, hb, meta, fbv, &meta->fb2_count, n, ctx->cus,
-                                  s));
+        GMLS_HIP(launch_fp64_wave(dim, order, GMLS_BASIS_DIVFREE, p_v, list, hb, meta, n, ctx->cus, s));
     } else {
       for (int b = 1; b < kNumBins; ++b)
         if (!sync || hm.count[b] > 0)
           GMLS_HIP(qr_bin(ctx, opt, dim, order, 0, b, sync ? hm.count[b] : n, as, &av, list, meta, s));
     }
     if (report) GMLS_HIP(hipEventRecord(ctx->ev[2], s));
-    GMLS_HIP(launch_qr_fallback(dim, order, GMLS_BASIS_SCALAR, as, fbs, meta, 4, ctx->cus * 8, s));
-    GMLS_HIP(launch_qr_queue(dim, order, GMLS_BASIS_DIVFREE, av, fbv, &meta->fb2_count, &meta->fb2_cursor,
-                             ctx->cus * 8, s));
+    if (ws && (!sync || hm.count[kLongBin] > 0))
+      GMLS_HIP(qr_bin(ctx, opt, dim, order, 0, kLongBin, sync ? hm.count[kLongBin] : n, as, &av, list, meta, s));
+    GMLS_HIP(qr_left(ctx, opt, dim, order, GMLS_BASIS_SCALAR, p_s, list, hb, meta, n, false, s));
+    GMLS_HIP(qr_left(ctx, opt, dim, order, GMLS_BASIS_DIVFREE, p_v, list, hb, meta, n, !ws && !pv, s));
   } else if (scheme < 0) {
     for (int b = 1; b < kNumBins; ++b) {
       if (sync && hm.count[b] == 0) continue;

@@ -156,6 +156,9 @@ struct BinMeta {
   int aux_cursor;  // their own sample matrix (scalar basis not unisolvent)
   int fb2_count;   // second set of a shared call (gmls_stencils_multi):
   int fb2_cursor;  // its FP64 fallback queue
+  // targets per bin that the FP64 kernels of many targets leave to QR (second
+  // row: the second set of a shared call)
+  int left[2][8];
 };
 
 // Per-call statistics accumulated on the device (mixed path).
@@ -225,15 +228,15 @@ hipError_t launch_mixed_pipe(int dim, int order, int basis, const StencilArgs &a
                              PipeTimer *timer, hipStream_t s);
 // FP64 pipeline (scalar, staggered and constrained stencils of bases with at
 // most 20 monomials; divergence-free bases whose scalar basis has at most 10)
-// in windows of `chunk` list slots; a set's targets that it does not take go
-// to the set's queue.  ss, sv: a scalar and a divergence-free set, or one of
-// them and null.  mom [chunk][moments], coef and sums [chunk][right-hand sides]
+// in windows of `chunk` list slots; the targets of bin b that it does not take
+// go to left_list[offset of the bin ..], counted in left[b].  ss, sv: a scalar
+// and a divergence-free set, or one of them and null.  mom [chunk][moments], coef and sums [chunk][right-hand sides]
 // [Q] (the larger of the sets'; every component of a divergence-free row is
 // one), rec [chunk] records.
 struct Pipe64Set {
   StencilArgs a;
-  int *fb_list;
-  int *fb_count;
+  int *left_list;
+  int *left;
 };
 bool pipe64_supported(int dim, int order, int basis);
 hipError_t launch_fp64_pipe(int dim, int order, const Pipe64Set *ss, const Pipe64Set *sv, const int *list,
@@ -241,13 +244,16 @@ hipError_t launch_fp64_pipe(int dim, int order, const Pipe64Set *ss, const Pipe6
                             int64_t chunk, int n_max, int cus, hipStream_t s);
 // FP64 with a wavefront per target and the corrected step: the bases that the
 // pipeline does not hold, alone or (_shared, where that is the scalar basis
-// too) a scalar with the divergence-free set of the same order; queues as above
+// too) a scalar with the divergence-free set of the same order; queues as
+// above; bins 1 .. 4 (rows over 256 are the QR kernel's)
 bool wave64_supported(int dim, int order, int basis);
-hipError_t launch_fp64_wave(int dim, int order, int basis, const StencilArgs &a, const int *list, const BinMeta *hm,
-                            BinMeta *meta, int *fb, int *fb_count, int n_max, int cus, hipStream_t s);
-hipError_t launch_fp64_wave_shared(int dim, int order, const StencilArgs &as, int *fbs, int *fbs_count,
-                                   const StencilArgs &av, int *fbv, int *fbv_count, const int *list, const BinMeta *hm,
-                                   BinMeta *meta, int n_max, int cus, hipStream_t s);
+hipError_t launch_fp64_wave(int dim, int order, int basis, const Pipe64Set &set, const int *list, const BinMeta *hm,
+                            BinMeta *meta, int n_max, int cus, hipStream_t s);
+hipError_t launch_fp64_wave_shared(int dim, int order, const Pipe64Set &ss, const Pipe64Set &sv, const int *list,
+                                   const BinMeta *hm, BinMeta *meta, int n_max, int cus, hipStream_t s);
+// the QR kernel on a bin's left targets (shape as in launch_qr_bin)
+hipError_t launch_qr_left(int dim, int order, int basis, int bin, int rpl, int wpe, const Pipe64Set &set, BinMeta *meta,
+                          int n_blocks, hipStream_t s);
 // targets from which an FP64 call takes these, and the most of them the
 // pipeline's buffers hold at a time (at most 3.8 KB each)
 constexpr int kFp64FastMin = 12288;

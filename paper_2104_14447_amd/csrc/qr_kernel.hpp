@@ -17,11 +17,13 @@ constexpr int qr_lds_doubles() {
   return SOLVE > kSumBufDoubles ? SOLVE : kSumBufDoubles;
 }
 
-// The target after a wave's first (which is its block's index): the rest are
-// taken in turn from the cursor.  A queue shorter than the grid touches no
-// cursor at all: the fallback's is usually empty, and the atomics of its 2048
-// waves on one word took 28 us a launch (5 us without).
-__device__ __forceinline__ int next_target(int n, int *cursor) {
+// The target after a wave's target i (its first is its block's index): the
+// rest are taken in turn from the cursor, or, where there is none, one grid
+// further on.  A queue shorter than the grid touches no cursor at all: the
+// fallback's is usually empty, and the atomics of its 2048 waves on one word
+// took 28 us a launch (5 us without).
+__device__ __forceinline__ int next_target(int i0, int n, int *cursor) {
+  if (!cursor) return i0 + (int)gridDim.x;
   if (n <= (int)gridDim.x) return n;
   int i = 0;
   if (lane_id() == 0) i = atomicAdd(cursor, 1);
@@ -36,7 +38,7 @@ __device__ __forceinline__ void qr_loop(const StencilArgs &a, const int *list, c
   const RowKinds rk = row_kinds(DIM, BASIS == 1 ? 1 : 0, a.mask);
   const int n = readfirstlane_i(*count);
   const int off = readfirstlane_i(offset ? *offset : 0);
-  for (int i = blockIdx.x; i < n; i = next_target(n, cursor)) {
+  for (int i = blockIdx.x; i < n; i = next_target(i, n, cursor)) {
     const int t = readfirstlane_i(list[off + i]);
     if constexpr (BASIS == 0)
       qr_scalar_target<DIM, ORDER, RPL>(a, rk, t, lds);
@@ -78,7 +80,7 @@ __device__ __forceinline__ void qr_shared_loop(const StencilArgs &as, const Sten
   const RowKinds rkv = row_kinds(DIM, 1, av.mask);
   const int n = readfirstlane_i(*count);
   const int off = readfirstlane_i(offset ? *offset : 0);
-  for (int i = blockIdx.x; i < n; i = next_target(n, cursor)) {
+  for (int i = blockIdx.x; i < n; i = next_target(i, n, cursor)) {
     const int t = readfirstlane_i(list[off + i]);
     Rows<DIM, RPL> r;
     double M[RPL][Q];

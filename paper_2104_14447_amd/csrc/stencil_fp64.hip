@@ -126,6 +126,12 @@ hipError_t launch_qr_bin(int dim, int order, int basis, int bin, int rpl, int wp
                      n_blocks, s);
 }
 
+hipError_t launch_qr_left(int dim, int order, int basis, int bin, int rpl, int wpe, const Pipe64Set &set, BinMeta *meta,
+                          int n_blocks, hipStream_t s) {
+  return dispatch_qr(dim, order, basis, rpl, wpe, set.a, set.left_list, set.left + bin, meta->offset + bin, nullptr,
+                     n_blocks, s);
+}
+
 hipError_t launch_qr_queue(int dim, int order, int basis, const StencilArgs &a, const int *list, const int *count,
                            int *cursor, int n_blocks, hipStream_t s) {
   return dispatch_qr(dim, order, basis, 4, 0, a, list, count, nullptr, cursor, n_blocks, s);

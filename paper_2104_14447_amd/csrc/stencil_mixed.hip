@@ -170,61 +170,44 @@ static const SharedFn kShared[2][4] = {
     {launch_wave_shared_d2_o1, launch_wave_shared_d2_o2, launch_wave_shared_d2_o3, launch_wave_shared_d2_o4},
     {launch_wave_shared_d3_o1, launch_wave_shared_d3_o2, launch_wave_shared_d3_o3, launch_wave_shared_d3_o4}};
 
-hipError_t launch_wave64_d2_o1_b0(const StencilArgs &, const int *, const BinMeta *, BinMeta *, int *, int *, int,
-                                  int, hipStream_t);
-hipError_t launch_wave64_d2_o1_b1(const StencilArgs &, const int *, const BinMeta *, BinMeta *, int *, int *, int,
-                                  int, hipStream_t);
-hipError_t launch_wave64_shared_d2_o1(const StencilArgs &, int *, int *, const StencilArgs &, int *, int *, const int *,
-                                     const BinMeta *, BinMeta *, int, int, hipStream_t);
-hipError_t launch_wave64_d2_o2_b0(const StencilArgs &, const int *, const BinMeta *, BinMeta *, int *, int *, int,
-                                  int, hipStream_t);
-hipError_t launch_wave64_d2_o2_b1(const StencilArgs &, const int *, const BinMeta *, BinMeta *, int *, int *, int,
-                                  int, hipStream_t);
-hipError_t launch_wave64_shared_d2_o2(const StencilArgs &, int *, int *, const StencilArgs &, int *, int *, const int *,
-                                     const BinMeta *, BinMeta *, int, int, hipStream_t);
-hipError_t launch_wave64_d2_o3_b0(const StencilArgs &, const int *, const BinMeta *, BinMeta *, int *, int *, int,
-                                  int, hipStream_t);
-hipError_t launch_wave64_d2_o3_b1(const StencilArgs &, const int *, const BinMeta *, BinMeta *, int *, int *, int,
-                                  int, hipStream_t);
-hipError_t launch_wave64_shared_d2_o3(const StencilArgs &, int *, int *, const StencilArgs &, int *, int *, const int *,
-                                     const BinMeta *, BinMeta *, int, int, hipStream_t);
-hipError_t launch_wave64_d2_o4_b0(const StencilArgs &, const int *, const BinMeta *, BinMeta *, int *, int *, int,
-                                  int, hipStream_t);
-hipError_t launch_wave64_d2_o4_b1(const StencilArgs &, const int *, const BinMeta *, BinMeta *, int *, int *, int,
-                                  int, hipStream_t);
-hipError_t launch_wave64_shared_d2_o4(const StencilArgs &, int *, int *, const StencilArgs &, int *, int *, const int *,
-                                     const BinMeta *, BinMeta *, int, int, hipStream_t);
-hipError_t launch_wave64_d3_o1_b0(const StencilArgs &, const int *, const BinMeta *, BinMeta *, int *, int *, int,
-                                  int, hipStream_t);
-hipError_t launch_wave64_d3_o1_b1(const StencilArgs &, const int *, const BinMeta *, BinMeta *, int *, int *, int,
-                                  int, hipStream_t);
-hipError_t launch_wave64_shared_d3_o1(const StencilArgs &, int *, int *, const StencilArgs &, int *, int *, const int *,
-                                     const BinMeta *, BinMeta *, int, int, hipStream_t);
-hipError_t launch_wave64_d3_o2_b0(const StencilArgs &, const int *, const BinMeta *, BinMeta *, int *, int *, int,
-                                  int, hipStream_t);
-hipError_t launch_wave64_d3_o2_b1(const StencilArgs &, const int *, const BinMeta *, BinMeta *, int *, int *, int,
-                                  int, hipStream_t);
-hipError_t launch_wave64_shared_d3_o2(const StencilArgs &, int *, int *, const StencilArgs &, int *, int *, const int *,
-                                     const BinMeta *, BinMeta *, int, int, hipStream_t);
-hipError_t launch_wave64_d3_o3_b0(const StencilArgs &, const int *, const BinMeta *, BinMeta *, int *, int *, int,
-                                  int, hipStream_t);
-hipError_t launch_wave64_d3_o3_b1(const StencilArgs &, const int *, const BinMeta *, BinMeta *, int *, int *, int,
-                                  int, hipStream_t);
-hipError_t launch_wave64_shared_d3_o3(const StencilArgs &, int *, int *, const StencilArgs &, int *, int *, const int *,
-                                     const BinMeta *, BinMeta *, int, int, hipStream_t);
-hipError_t launch_wave64_d3_o4_b0(const StencilArgs &, const int *, const BinMeta *, BinMeta *, int *, int *, int,
-                                  int, hipStream_t);
-hipError_t launch_wave64_d3_o4_b1(const StencilArgs &, const int *, const BinMeta *, BinMeta *, int *, int *, int,
-                                  int, hipStream_t);
-hipError_t launch_wave64_shared_d3_o4(const StencilArgs &, int *, int *, const StencilArgs &, int *, int *, const int *,
-                                     const BinMeta *, BinMeta *, int, int, hipStream_t);
-using Wave64Fn = hipError_t (*)(const StencilArgs &, const int *, const BinMeta *, BinMeta *, int *, int *, int, int,
-                                hipStream_t);
+hipError_t launch_wave64_d2_o1_b0(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
+hipError_t launch_wave64_d2_o1_b1(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
+hipError_t launch_wave64_shared_d2_o1(const Pipe64Set &, const Pipe64Set &, const int *, const BinMeta *, BinMeta *,
+                                     int, int, hipStream_t);
+hipError_t launch_wave64_d2_o2_b0(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
+hipError_t launch_wave64_d2_o2_b1(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
+hipError_t launch_wave64_shared_d2_o2(const Pipe64Set &, const Pipe64Set &, const int *, const BinMeta *, BinMeta *,
+                                     int, int, hipStream_t);
+hipError_t launch_wave64_d2_o3_b0(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
+hipError_t launch_wave64_d2_o3_b1(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
+hipError_t launch_wave64_shared_d2_o3(const Pipe64Set &, const Pipe64Set &, const int *, const BinMeta *, BinMeta *,
+                                     int, int, hipStream_t);
+hipError_t launch_wave64_d2_o4_b0(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
+hipError_t launch_wave64_d2_o4_b1(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
+hipError_t launch_wave64_shared_d2_o4(const Pipe64Set &, const Pipe64Set &, const int *, const BinMeta *, BinMeta *,
+                                     int, int, hipStream_t);
+hipError_t launch_wave64_d3_o1_b0(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
+hipError_t launch_wave64_d3_o1_b1(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
+hipError_t launch_wave64_shared_d3_o1(const Pipe64Set &, const Pipe64Set &, const int *, const BinMeta *, BinMeta *,
+                                     int, int, hipStream_t);
+hipError_t launch_wave64_d3_o2_b0(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
+hipError_t launch_wave64_d3_o2_b1(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
+hipError_t launch_wave64_shared_d3_o2(const Pipe64Set &, const Pipe64Set &, const int *, const BinMeta *, BinMeta *,
+                                     int, int, hipStream_t);
+hipError_t launch_wave64_d3_o3_b0(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
+hipError_t launch_wave64_d3_o3_b1(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
+hipError_t launch_wave64_shared_d3_o3(const Pipe64Set &, const Pipe64Set &, const int *, const BinMeta *, BinMeta *,
+                                     int, int, hipStream_t);
+hipError_t launch_wave64_d3_o4_b0(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
+hipError_t launch_wave64_d3_o4_b1(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
+hipError_t launch_wave64_shared_d3_o4(const Pipe64Set &, const Pipe64Set &, const int *, const BinMeta *, BinMeta *,
+                                     int, int, hipStream_t);
+using Wave64Fn = hipError_t (*)(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
 static const Wave64Fn kWave64[2][4][2] = {
     {{launch_wave64_d2_o1_b0, launch_wave64_d2_o1_b1}, {launch_wave64_d2_o2_b0, launch_wave64_d2_o2_b1}, {launch_wave64_d2_o3_b0, launch_wave64_d2_o3_b1}, {launch_wave64_d2_o4_b0, launch_wave64_d2_o4_b1}},
     {{launch_wave64_d3_o1_b0, launch_wave64_d3_o1_b1}, {launch_wave64_d3_o2_b0, launch_wave64_d3_o2_b1}, {launch_wave64_d3_o3_b0, launch_wave64_d3_o3_b1}, {launch_wave64_d3_o4_b0, launch_wave64_d3_o4_b1}}};
-using Shared64Fn = hipError_t (*)(const StencilArgs &, int *, int *, const StencilArgs &, int *, int *, const int *,
-                                  const BinMeta *, BinMeta *, int, int, hipStream_t);
+using Shared64Fn = hipError_t (*)(const Pipe64Set &, const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int,
+                                  hipStream_t);
 static const Shared64Fn kShared64[2][4] = {
     {launch_wave64_shared_d2_o1, launch_wave64_shared_d2_o2, launch_wave64_shared_d2_o3, launch_wave64_shared_d2_o4},
     {launch_wave64_shared_d3_o1, launch_wave64_shared_d3_o2, launch_wave64_shared_d3_o3, launch_wave64_shared_d3_o4}};
@@ -301,17 +284,16 @@ bool wave64_supported(int dim, int order, int basis) {
          !pipe64_supported(dim, order, basis);
 }
 
-hipError_t launch_fp64_wave(int dim, int order, int basis, const StencilArgs &a, const int *list, const BinMeta *hm,
-                            BinMeta *meta, int *fb, int *fb_count, int n_max, int cus, hipStream_t s) {
+hipError_t launch_fp64_wave(int dim, int order, int basis, const Pipe64Set &set, const int *list, const BinMeta *hm,
+                            BinMeta *meta, int n_max, int cus, hipStream_t s) {
   if (!wave64_supported(dim, order, basis)) return hipErrorInvalidValue;
-  return kWave64[dim - 2][order - 1][basis](a, list, hm, meta, fb, fb_count, n_max, cus, s);
+  return kWave64[dim - 2][order - 1][basis](set, list, hm, meta, n_max, cus, s);
 }
 
-hipError_t launch_fp64_wave_shared(int dim, int order, const StencilArgs &as, int *fbs, int *fbs_count,
-                                   const StencilArgs &av, int *fbv, int *fbv_count, const int *list, const BinMeta *hm,
-                                   BinMeta *meta, int n_max, int cus, hipStream_t s) {
+hipError_t launch_fp64_wave_shared(int dim, int order, const Pipe64Set &ss, const Pipe64Set &sv, const int *list,
+                                   const BinMeta *hm, BinMeta *meta, int n_max, int cus, hipStream_t s) {
   if (!wave64_supported(dim, order, 0)) return hipErrorInvalidValue;
-  return kShared64[dim - 2][order - 1](as, fbs, fbs_count, av, fbv, fbv_count, list, hm, meta, n_max, cus, s);
+  return kShared64[dim - 2][order - 1](ss, sv, list, hm, meta, n_max, cus, s);
 }
 
 hipError_t launch_mixed_bin(int dim, int order, int basis, int bin, const StencilArgs &a, const int *list,

@@ -71,6 +71,25 @@ __device__ __forceinline__ SlotRange slot_range(const BinMeta *meta, int bin, in
   return {readfirstlane_i(lo), readfirstlane_i(hi), readfirstlane_i(c0)};
 }
 
+// The FP64 path's queues: the targets t of list slots `slot` that a lane leaves
+// to the QR kernel, in their bin's part of left_list (in any order), one atomic
+// per wavefront and bin.  All lanes take part.
+__device__ __forceinline__ void leave_targets(bool leave, int slot, int t, const BinMeta *meta, int *left_list,
+                                              int *left) {
+  if (__ballot(leave) == 0) return;
+  for (int b = 1; b < kNumBins; ++b) {
+    const int lo = meta->offset[b];
+    uint64_t m;
+    const bool mine = leave && slot >= lo && slot < lo + meta->count[b];
+    const int k = ballot_prefix(mine, &m);
+    if (m == 0) continue;
+    int base = 0;
+    if (lane_id() == 0) base = atomicAdd(left + b, __popcll(m));
+    base = lo + __builtin_amdgcn_readfirstlane(base);
+    if (mine) left_list[base + k] = t;
+  }
+}
+
 template <int DIM>
 __global__ __launch_bounds__(256) void k_pipe_prep(StencilArgs a, const int *list, const BinMeta *meta, int win_lo,
                                                    int win_hi, PipeRec *rec) {
@@ -621,6 +640,7 @@ __global__ __launch_bounds__(64) void k_pipe_weights(StencilArgs a, const PipeRe
     const int64_t loc = (valid ? i : first) - c0;
     const PipeRec rc = rec[loc];
     const bool good = valid && rc.ok;
+    if (__ballot(good) == 0) continue;  // no target to form weights of
     const double *y0 = yin + (int64_t)(i0 - c0) * ys;
     CoefFetch<TPW, Q> cq;
     cq.fetch(y0, ys, last - i0);
@@ -703,8 +723,8 @@ __global__ __launch_bounds__(64) void k_pipe_weights(StencilArgs a, const PipeRe
 // divergence-free fit is identically zero: its g is 0.
 //
 // The FP64 path runs the solve kernel twice (stencil_pipe64.hpp): PASS 0 as
-// above, a pivot at or below kCholTol of its diagonal entry sending the
-// target to the QR kernel; PASS 1 corrects g with the residual taken over the
+// above, a pivot at or below kCholTol of its diagonal entry leaving the
+// target to the QR kernel (fb_list, fb_count: its queues by bin); PASS 1 corrects g with the residual taken over the
 // rows, sums [slot][F][DIM][QS] = P^T (W P g_k) on the plain monomials: per
 // component c, rho_k = delta_(k,c) l - G_s g_k - D_k^T t, dv_k = G_s^-1 rho_k,
 // S dt = D (dv + g), g_k += dv_k - G_s^-1 D_k^T dt.
@@ -961,8 +981,11 @@ __global__ __launch_bounds__(64) void k_pipe_solve_div(StencilArgs a, PipeRec *r
       a.status[t] = good ? GMLS_TARGET_OK : GMLS_TARGET_FALLBACK;
       rec[sl - c0].ok = good ? 1 : 0;
     }
+    if constexpr (PASS >= 0) {
+      leave_targets(fell, sl, t, meta, fb_list, fb_count);
+      continue;  // the mixed path's statistics follow
+    }
     if (fell) fb_list[atomicAdd(fb_count, 1)] = t;
-    if constexpr (PASS >= 0) continue;  // the mixed path's statistics follow
     const unsigned long long mg = __ballot(good), mfb = __ballot(fell);
     if (lane == 0 && mg) atomicAdd(&stats->sweep_hist[0], (unsigned long long)__popcll(mg));
     if (lane == 0 && mfb) atomicAdd(&stats->n_fallback, (unsigned long long)__popcll(mfb));
@@ -1003,6 +1026,7 @@ __global__ __launch_bounds__(64) void k_pipe_weights_div(StencilArgs a, const Pi
     const int64_t loc = (valid ? i : first) - c0;
     const PipeRec rc = rec[loc];
     const bool good = valid && rc.ok;
+    if (__ballot(good) == 0) continue;  // no target to form weights of
     const int64_t base = rc.base;
     const int N = rc.n;
     double xt[DIM];

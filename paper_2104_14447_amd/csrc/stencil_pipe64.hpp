@@ -175,7 +175,7 @@ __device__ __forceinline__ void quad_solve(const double (&M)[QuadTri<Q>::N], dou
 template <int DIM, int ORDER, int SKIP, int PASS>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_pipe_chol(
     StencilArgs a, PipeRec *rec, int win_lo, int win_hi, const double *mom, double *coef, const double *sums,
-    int *fb_list, int *fb_count, BinMeta *meta) {
+    int *left_list, int *left, BinMeta *meta) {
 #pragma clang fp contract(off)
   constexpr int Q = num_mono(DIM, ORDER) - SKIP;
   constexpr int NM = num_mono(DIM, 2 * ORDER);
@@ -210,6 +210,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
     const int t = rec[loc].t;
     const double ie = rec[loc].ie;
     const bool use = valid && (PASS == 0 || rec[loc].ok);
+    if constexpr (PASS == 1) {
+      if (__ballot(use) == 0) continue;  // left to the QR kernel, all of them
+    }
     // row i = 4 q + l: its moments' indices, a byte per lane of the quad
     const double *mt = mls + tq * NM;
     double M[T::N], diag[T::QB];
@@ -334,11 +337,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
     if constexpr (PASS == 0) {
       if (valid && l == 0) {
         rec[loc].ok = ok ? 1 : 0;
-        if (ok)
-          a.status[t] = GMLS_TARGET_OK;
-        else
-          fb_list[atomicAdd(fb_count, 1)] = t;
+        if (ok) a.status[t] = GMLS_TARGET_OK;
       }
+      leave_targets(valid && l == 0 && !ok, s0 + tq, t, meta, left_list, left);
     }
     wave_lds_sync();  // the moments' buffer is rewritten
   }
@@ -371,6 +372,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
     const bool valid = i < last;
     const int64_t loc = (valid ? i : first) - c0;
     const PipeRec rc = rec[loc];
+    if (__ballot(valid && rc.ok) == 0) continue;  // left to the QR kernel, all of them
     const int64_t base = rc.base;
     const int N = rc.n;
     double xt[DIM];
@@ -513,10 +515,10 @@ hipError_t launch_pipe64(const Pipe64Set *ss, const Pipe64Set *sv, const int *li
       if (nbc > cus * 64) nbc = cus * 64;
       nbc = xcd_grid(nbc);
       k_pipe_chol<DIM, ORDER, SKIP, 0>
-          <<<nbc, 64, 0, s>>>(ss->a, rec, win_lo, win_hi, mom, coef, sums, ss->fb_list, ss->fb_count, meta);
+          <<<nbc, 64, 0, s>>>(ss->a, rec, win_lo, win_hi, mom, coef, sums, ss->left_list, ss->left, meta);
       pipe64_bins<DIM, ORDER, SKIP, 0>(1, ss->a, rec, hm, meta, win_lo, win_hi, mom, coef, sums, cus, s);
       k_pipe_chol<DIM, ORDER, SKIP, 1>
-          <<<nbc, 64, 0, s>>>(ss->a, rec, win_lo, win_hi, mom, coef, sums, ss->fb_list, ss->fb_count, meta);
+          <<<nbc, 64, 0, s>>>(ss->a, rec, win_lo, win_hi, mom, coef, sums, ss->left_list, ss->left, meta);
       pipe64_bins<DIM, ORDER, SKIP, 0>(2, ss->a, rec, hm, meta, win_lo, win_hi, mom, coef, sums, cus, s);
     }
     if constexpr (SKIP == 0 && has_pipe_div<DIM, ORDER>()) {
@@ -526,11 +528,11 @@ hipError_t launch_pipe64(const Pipe64Set *ss, const Pipe64Set *sv, const int *li
         nbs = xcd_grid(nbs);
         StencilArgs each = sv->a;  // every component of every row as a right-hand side of its own
         each.F = sv->a.F * DIM;
-        k_pipe_solve_div<DIM, ORDER, 0><<<nbs, 64, 0, s>>>(sv->a, rec, win_lo, win_hi, mom, coef, sums, sv->fb_list,
-                                                           sv->fb_count, meta, nullptr, Options());
+        k_pipe_solve_div<DIM, ORDER, 0><<<nbs, 64, 0, s>>>(sv->a, rec, win_lo, win_hi, mom, coef, sums, sv->left_list,
+                                                           sv->left, meta, nullptr, Options());
         pipe64_bins<DIM, ORDER, 0, 0>(1, each, rec, hm, meta, win_lo, win_hi, mom, coef, sums, cus, s);
-        k_pipe_solve_div<DIM, ORDER, 1><<<nbs, 64, 0, s>>>(sv->a, rec, win_lo, win_hi, mom, coef, sums, sv->fb_list,
-                                                           sv->fb_count, meta, nullptr, Options());
+        k_pipe_solve_div<DIM, ORDER, 1><<<nbs, 64, 0, s>>>(sv->a, rec, win_lo, win_hi, mom, coef, sums, sv->left_list,
+                                                           sv->left, meta, nullptr, Options());
         pipe64_bins<DIM, ORDER, 0, 1>(2, sv->a, rec, hm, meta, win_lo, win_hi, mom, coef, sums, cus, s);
       }
     }

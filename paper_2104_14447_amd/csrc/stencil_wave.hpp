@@ -421,7 +421,8 @@ struct WaveCounts {
   double cond = 0.0;
 };
 
-// Queue of one stencil set: its arguments, fallback list and counter.
+// Queue of one stencil set: its arguments, fallback list and counter (FP64
+// path: the list in parts by bin, a counter per bin).
 struct WaveSet {
   StencilArgs a;
   int *fb_list;
@@ -920,6 +921,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveCand[CA
   const RowKinds rks = row_kinds(DIM, 0, ss.a.mask), rkv = row_kinds(DIM, 1, sv.a.mask);
   WaveCounts cnt, cntv;
   const SlotRange R = slot_range(meta, bin, -1, INT_MAX);
+  const int left0 = R.first;  // the bin's part of the FP64 path's queues
   for (int i = R.first + xcd_block(); i < R.last; i += gridDim.x) {
     const int t = list[i];
     const int64_t base = a.row_ptr[t];
@@ -988,7 +990,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveCand[CA
       if (ok) wave_scalar_weights<DIM, ORDER, RPL>(ss.a, base, N, s, w, cfs);
       if (lane == 0) {
         ss.a.status[t] = ok ? GMLS_TARGET_OK : GMLS_TARGET_FALLBACK;
-        if (!ok) ss.fb_list[atomicAdd(ss.fb_count, 1)] = t;
+        if (!ok) ss.fb_list[REF ? left0 + atomicAdd(ss.fb_count + bin, 1) : atomicAdd(ss.fb_count, 1)] = t;
       }
     }
     if constexpr (DIVF) {
@@ -996,7 +998,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveCand[CA
         if (okv) wave_divfree_weights<DIM, ORDER, RPL>(sv.a, rkv, base, N, s, w, big);
       if (lane == 0) {
         sv.a.status[t] = okv ? GMLS_TARGET_OK : GMLS_TARGET_FALLBACK;
-        if (!okv) sv.fb_list[atomicAdd(sv.fb_count, 1)] = t;
+        if (!okv) sv.fb_list[REF ? left0 + atomicAdd(sv.fb_count + bin, 1) : atomicAdd(sv.fb_count, 1)] = t;
       }
     }
     __syncthreads();
@@ -1074,25 +1076,16 @@ hipError_t launch_wave(const WaveSet &ss, const WaveSet &sv, const int *list, co
   return hipGetLastError();
 }
 
-// The FP64 path: as launch_wave, in the default variant.
+// The FP64 path: as launch_wave, in the default variant, without the long bin.
 template <int DIM, int ORDER, int BASIS>
 hipError_t launch_wave64(const WaveSet &ss, const WaveSet &sv, const int *list, const BinMeta *hm, BinMeta *meta,
                          int n_max, int cus, hipStream_t s) {
   const Options opt;
-  for (int b = 1; b < kNumBins; ++b) {
+  for (int b = 1; b < kLongBin; ++b) {
     int cnt = n_max;
     if (hm) {
       cnt = hm->count[b];
       if (cnt == 0) continue;
-    }
-    if (b == kLongBin) {  // rows over 256: the QR kernels take them in chunks
-      hipError_t e = hipSuccess;
-      if constexpr (BASIS == 0 || BASIS == 3)
-        e = launch_defer_bin(ss.a.status, list, meta, b, ss.fb_list, ss.fb_count, nullptr, s);
-      if constexpr (BASIS == 1 || BASIS == 3)
-        if (e == hipSuccess) e = launch_defer_bin(sv.a.status, list, meta, b, sv.fb_list, sv.fb_count, nullptr, s);
-      if (e != hipSuccess) return e;
-      continue;
     }
     const int nb = xcd_grid(cnt < cus * 16 ? cnt : cus * 16);
     switch (b) {

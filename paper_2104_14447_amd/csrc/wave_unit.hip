@@ -32,9 +32,9 @@ hipError_t GMLS_WAVE_FN(const StencilArgs &a, const int *list, const BinMeta *hm
   return launch_wave<GMLS_DIM, GMLS_ORDER, GMLS_BASIS>(one, one, list, hm, meta, stats, opt, n_max, cus, timer, s);
 }
 
-hipError_t GMLS_WAVE64_FN(const StencilArgs &a, const int *list, const BinMeta *hm, BinMeta *meta, int *fb, int *fb_count,
-                          int n_max, int cus, hipStream_t s) {
-  const WaveSet one{a, fb, fb_count};
+hipError_t GMLS_WAVE64_FN(const Pipe64Set &set, const int *list, const BinMeta *hm, BinMeta *meta, int n_max, int cus,
+                          hipStream_t s) {
+  const WaveSet one{set.a, set.left_list, set.left};
   if constexpr (GMLS_BASIS == 1 ? !has_pipe_div<GMLS_DIM, GMLS_ORDER>() : !has_pipe<GMLS_DIM, GMLS_ORDER>())
     return launch_wave64<GMLS_DIM, GMLS_ORDER, GMLS_BASIS>(one, one, list, hm, meta, n_max, cus, s);
   else
@@ -51,10 +51,9 @@ hipError_t GMLS_SHARED_FN(const StencilArgs &as, int *fbs, int *fbs_count, const
   return launch_wave<GMLS_DIM, GMLS_ORDER, 3>(ss, sv, list, hm, meta, stats, opt, n_max, cus, timer, s);
 }
 
-hipError_t GMLS_SHARED64_FN(const StencilArgs &as, int *fbs, int *fbs_count, const StencilArgs &av, int *fbv,
-                            int *fbv_count, const int *list, const BinMeta *hm, BinMeta *meta, int n_max, int cus,
-                            hipStream_t s) {
-  const WaveSet ss{as, fbs, fbs_count}, sv{av, fbv, fbv_count};
+hipError_t GMLS_SHARED64_FN(const Pipe64Set &s0, const Pipe64Set &s1, const int *list, const BinMeta *hm, BinMeta *meta,
+                            int n_max, int cus, hipStream_t s) {
+  const WaveSet ss{s0.a, s0.left_list, s0.left}, sv{s1.a, s1.left_list, s1.left};
   if constexpr (!has_pipe<GMLS_DIM, GMLS_ORDER>())
     return launch_wave64<GMLS_DIM, GMLS_ORDER, 3>(ss, sv, list, hm, meta, n_max, cus, s);
   else
