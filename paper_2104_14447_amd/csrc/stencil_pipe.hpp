@@ -730,6 +730,14 @@ __global__ __launch_bounds__(64) void k_pipe_weights(StencilArgs a, const PipeRe
 // S dt = D (dv + g), g_k += dv_k - G_s^-1 D_k^T dt.
 // ---------------------------------------------------------------------------
 constexpr double kCholTol = 1e-6;
+// A small pivot shows a large condition number, a large condition number need
+// not show in any pivot: what bounds it is the correction itself, whose size
+// relative to the solution (both in the norm of the equilibrated system) is the
+// first solve's error, some cond(M) 2^-54.  Above this bound (cond(M) of some
+// 2e8, 1.5e4 for the weighted sample matrix) the target is left to QR.  By the
+// pivots alone 1200 one-sided 2-D order-4 targets of 15 neighbours had errors
+// up to 7.5e-7, QR's at most 1e-9.
+constexpr double kCorrTol = 0x1p-27;
 
 template <int DIM, int ORDER>
 struct DivUp {
@@ -897,6 +905,7 @@ __global__ __launch_bounds__(64) void k_pipe_solve_div(StencilArgs a, PipeRec *r
       }
     const bool s_ok = packed_cholesky64<QM, (PASS >= 0)>(S, PASS < 0 ? 1e-300 : kCholTol);
     if constexpr (PASS <= 0) ok = ok && s_ok;
+    bool small = true;  // PASS 1: every correction is (kCorrTol)
     for (int f = 0; f < F; ++f) {
       const int kind = rk.kind[f], comp = rk.comp[f];
       double g[DIM][QS];
@@ -913,6 +922,11 @@ __global__ __launch_bounds__(64) void k_pipe_solve_div(StencilArgs a, PipeRec *r
 #pragma unroll
         for (int i = 0; i < QS; ++i) x[i] = lam[i] * sc[i];
         packed_solve64<QS>(L, x);
+        double ev = 0.0, ed = 0.0;  // PASS 1: sizes of v and of the correction, equilibrated
+        if constexpr (PASS == 1) {
+#pragma unroll
+          for (int i = 0; i < QS; ++i) ev = fma(x[i], x[i], ev);
+        }
         double tv[QM];
 #pragma unroll
         for (int b = 0; b < QM; ++b) {
@@ -935,9 +949,14 @@ __global__ __launch_bounds__(64) void k_pipe_solve_div(StencilArgs a, PipeRec *r
             g[k][i] = v * sc[i];
           }
           packed_solve64<QS>(L, g[k]);
+          if constexpr (PASS == 1) {
+#pragma unroll
+            for (int i = 0; i < QS; ++i) ed = fma(g[k][i], g[k][i], ed);
+          }
 #pragma unroll
           for (int i = 0; i < QS; ++i) g[k][i] *= sc[i];
         }
+        if constexpr (PASS == 1) small = small && ed <= kCorrTol * kCorrTol * ev;
         if constexpr (PASS == 1) {
           // dv_k + g_k, then the constraint
 #pragma unroll
@@ -974,7 +993,12 @@ __global__ __launch_bounds__(64) void k_pipe_solve_div(StencilArgs a, PipeRec *r
           for (int i = 0; i < QS; ++i) gout[((loc * F + f) * DIM + k) * QS + i] = g[k][i] * IF.v[i];
       }
     }
-    if constexpr (PASS == 1) continue;
+    if constexpr (PASS == 1) {
+      const bool leave = ok && !small;
+      if (leave) rec[sl - c0].ok = 0;
+      leave_targets(leave, sl, t, meta, fb_list, fb_count);
+      continue;
+    }
     const bool good = valid && ok;
     const bool fell = valid && !ok;
     if (valid) {

@@ -20,8 +20,9 @@
 //     k_pipe_solve_div   the two B steps of the divergence-free basis
 //   C weights            that of the mixed pipeline
 // A target whose factor meets a pivot at or below kCholTol of its diagonal
-// entry (cond(M) above about 1e6, rank deficiency among it) goes to the QR
-// kernel, which also applies the rank test.
+// entry (rank deficiency among it), or whose correction is larger than kCorrTol
+// of its solution (cond(M) above about 2e8), goes to the QR kernel, which also
+// applies the rank test.
 //
 // Why not QR for every target: a wavefront per target spends its time in the
 // round trips of Q dependent column sums (2M targets of about 110 neighbours,
@@ -243,6 +244,20 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
       const uint64_t bad = __ballot(!ok);
       ok = ((bad >> (lane & ~3)) & 15u) == 0;
     }
+    // the sums over the quad of v_i^2 M_ii, entry 4 q + l on lane l
+    auto energy = [&](const double(&v)[T::QB]) {
+      double e = 0.0;
+#pragma unroll
+      for (int q = 0; q < T::QB; ++q) {
+        unsigned idx = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (4 * q + u < Q) idx |= (unsigned)SI.idx[4 * q + u + SKIP][4 * q + u + SKIP] << (8 * u);
+        if (4 * q + 3 < Q || 4 * q + l < Q) e = fma(v[q] * v[q], mt[(idx >> (8 * l)) & 255u], e);
+      }
+      return quad_sum(e);
+    };
+    bool good = true;  // PASS 1: every correction is small (kCorrTol)
     // right-hand side f (f == F: the constraint's row)
     auto rhs = [&](int f, double(&b)[T::QB]) {
 #pragma unroll
@@ -282,6 +297,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
           z[q] = 4 * q + l < Q ? coef[at(F, q)] + b[0][q] : 0.0;
           fr[q] = 0.0;
         }
+        good = energy(b[0]) <= kCorrTol * kCorrTol * energy(z);
 #pragma unroll
         for (int d = 0; d < DIM; ++d) fr[(1 + d) / 4] = l == (1 + d) % 4 ? a.normals[(int64_t)t * DIM + d] * ie : fr[(1 + d) / 4];
 #pragma unroll
@@ -297,6 +313,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
         c[q] = b[q];
         if constexpr (PASS == 1) c[q] += 4 * q + l < Q ? coef[at(f, q)] : 0.0;
       }
+      if constexpr (PASS == 1) good = good && energy(b) <= kCorrTol * kCorrTol * energy(c);
       if constexpr (SKIP == 0 && PASS == 1) {
         if (a.normals) {
           double fc = 0.0;
@@ -340,6 +357,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
         if (ok) a.status[t] = GMLS_TARGET_OK;
       }
       leave_targets(valid && l == 0 && !ok, s0 + tq, t, meta, left_list, left);
+    } else {
+      const bool leave = use && l == 0 && !good;
+      if (leave) rec[loc].ok = 0;
+      leave_targets(leave, s0 + tq, t, meta, left_list, left);
     }
     wave_lds_sync();  // the moments' buffer is rewritten
   }
