@@ -560,7 +560,7 @@ static gmls_status run_stencils(gmls_ctx ctx, const double *coords, int64_t n_sr
   const bool pipe64 = fast && pipe64_supported(dim, order, basis) &&
                       p64.get(ctx, dim, order,
                               basis == GMLS_BASIS_DIVFREE ? (size_t)F * C * binom_l(order + dim, dim)
-                                                          : (size_t)(F + (normals ? 1 : 0)) * Q,
+                                                          : (size_t)F * Q,
                               n);
   const bool wave64 = fast && !normals && wave64_supported(dim, order, basis);
   const Pipe64Set set{a, fb, meta->left[0]};

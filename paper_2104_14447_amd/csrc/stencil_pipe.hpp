@@ -631,9 +631,7 @@ __global__ __launch_bounds__(64) void k_pipe_weights(StencilArgs a, const PipeRe
   const int lane = lane_id();
   const int grp = lane / G, lg = lane % G;
   const int F = a.F;
-  // the coefficients of the plain monomials (constrained stencils hold one
-  // more right-hand side per target)
-  const int ys = (F + (a.normals ? 1 : 0)) * Q;
+  const int ys = F * Q;  // coefficients of a target's plain monomials
   for (int i0 = first + xcd_block() * TPW; i0 < last; i0 += gridDim.x * TPW) {
     const int i = i0 + grp;
     const bool valid = i < last;

@@ -166,13 +166,18 @@ __device__ __forceinline__ void quad_solve(const double (&M)[QuadTri<Q>::N], dou
 // pivots and columns pass between the lanes by DPP.  Bound by instruction
 // issue: a third are those moves (2 per double).  0.33 ms per million targets
 // and pass at order 3 and one right-hand side, 0.12 ms for each more; compiled
-// for three wavefronts per SIMD it spills and takes 2.6 times as long.  PASS 0: the factor and c = M^-1 lambda' of every
-// functional into coef [slot][Fp][Q] (Fp: the F functionals, and on
-// constrained stencils the constraint's row n . grad as one more).  PASS 1:
-// the same factor again (taking it once more costs less than 1.7 KB per
-// target through memory), c += M^-1 (lambda' - sums), then the constraint:
-// with z the constraint's solution and f its row, c -= (f.c / f.z) z and the
-// boundary weight f.c / f.z (Section 2.3).
+// for three wavefronts per SIMD it spills and takes 2.6 times as long.
+//
+// PASS 0: the factor and c = M^-1 lambda' of every functional into coef
+// [slot][F][Q].  PASS 1: the same factor again (taking it once more costs less
+// than 1.7 KB per target through memory) and c += M^-1 (lambda' - sums).  The
+// constraint f . c = 0 of the Neumann stencils is eliminated in both: with
+// z = M^-1 f, g = f.c / f.z is the boundary weight and c -= g z (Section 2.3);
+// PASS 1 corrects c and g together, from the residual lambda' - sums - g f, and
+// eliminates what the correction brings back.  Corrected apart from each other
+// c and z bring their own errors to the difference: root mean square errors of
+// one-sided 3-D order-3 targets, 24 neighbours 9.5e-14 (QR 9.0e-14), 80
+// neighbours 3.9e-15 (5.8e-15); corrected together 5.7e-15 and 8.1e-16.
 template <int DIM, int ORDER, int SKIP, int PASS>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_pipe_chol(
     StencilArgs a, PipeRec *rec, int win_lo, int win_hi, const double *mom, double *coef, const double *sums,
@@ -185,7 +190,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
   constexpr SumIndex<DIM, ORDER> SI{};
   __shared__ double mls[16 * NM];
   const int lane = lane_id(), l = lane & 3, tq = lane >> 2;
-  const int F = a.F, Fp = F + (a.normals ? 1 : 0);
+  const int F = a.F;
   const RowKinds rk = row_kinds(DIM, 0, a.mask);
   const SlotRange R = slot_range(meta, 0, win_lo, win_hi);
   const int first = R.first, last = R.last, c0 = R.c0;
@@ -258,7 +263,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
       return quad_sum(e);
     };
     bool good = true;  // PASS 1: every correction is small (kCorrTol)
-    // right-hand side f (f == F: the constraint's row)
+    // right-hand side f (PASS 1: its residual over the rows; the multiplier's
+    // part is taken off on constrained stencils)
     auto rhs = [&](int f, double(&b)[T::QB]) {
 #pragma unroll
       for (int q = 0; q < T::QB; ++q) {
@@ -267,41 +273,47 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
         for (int u = 0; u < 4; ++u) {
           const int i = 4 * q + u;
           if (i >= Q || i + SKIP > num_mono(DIM, ORDER < 2 ? ORDER : 2) - 1) continue;
-          double v;
-          if (f < F) {
-            v = plain_lambda<DIM, ORDER>(rk.kind[f], i + SKIP, ie);
-          } else {
-            v = i >= 1 && i <= DIM ? a.normals[(int64_t)t * DIM + i - 1] * ie : 0.0;
-          }
+          const double v = plain_lambda<DIM, ORDER>(rk.kind[f], i + SKIP, ie);
           b[q] = l == u ? v : b[q];
         }
         if constexpr (PASS == 1) {
           const int i = 4 * q + l;
-          if (i < Q) b[q] -= sums[(loc * Fp + f) * Q + i];
+          if (i < Q) b[q] -= sums[(loc * F + f) * Q + i];
+        }
+      }
+      if constexpr (SKIP == 0 && PASS == 1) {
+        if (a.normals) {
+          const double g = a.hweights[(int64_t)t * F + f];
+#pragma unroll
+          for (int d = 0; d < DIM; ++d)
+            b[(1 + d) / 4] -= l == (1 + d) % 4 ? g * (a.normals[(int64_t)t * DIM + d] * ie) : 0.0;
         }
       }
     };
     // entry i of the solution of right-hand side f
-    auto at = [&](int f, int q) { return (loc * Fp + f) * Q + 4 * q + l; };
-    double z[T::QB], fz = 0.0;
+    auto at = [&](int f, int q) { return (loc * F + f) * Q + 4 * q + l; };
+    // the constraint (SKIP 0): its row fr, z = M^-1 fr and fr . z
+    double z[T::QB], fr[T::QB], fz = 0.0;
     bool con = false;
-    if constexpr (SKIP == 0 && PASS == 1) {
+    if constexpr (SKIP == 0) {
       if (a.normals) {
-        for (int d = 0; d < DIM; ++d) con = con || a.normals[(int64_t)t * DIM + d] != 0.0;
-        double b[1][T::QB], fr[T::QB];
-        rhs(F, b[0]);
+        double b[1][T::QB];
+#pragma unroll
+        for (int q = 0; q < T::QB; ++q) fr[q] = 0.0;
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) {
+          const double v = a.normals[(int64_t)t * DIM + d];
+          con = con || v != 0.0;
+          fr[(1 + d) / 4] = l == (1 + d) % 4 ? v * ie : fr[(1 + d) / 4];
+        }
+#pragma unroll
+        for (int q = 0; q < T::QB; ++q) b[0][q] = fr[q];
         quad_solve<Q, 1>(M, b, l);
-        fz = 0.0;
 #pragma unroll
         for (int q = 0; q < T::QB; ++q) {
-          z[q] = 4 * q + l < Q ? coef[at(F, q)] + b[0][q] : 0.0;
-          fr[q] = 0.0;
+          z[q] = 4 * q + l < Q ? b[0][q] : 0.0;
+          fz = fma(fr[q], z[q], fz);
         }
-        good = energy(b[0]) <= kCorrTol * kCorrTol * energy(z);
-#pragma unroll
-        for (int d = 0; d < DIM; ++d) fr[(1 + d) / 4] = l == (1 + d) % 4 ? a.normals[(int64_t)t * DIM + d] * ie : fr[(1 + d) / 4];
-#pragma unroll
-        for (int q = 0; q < T::QB; ++q) fz = fma(fr[q], z[q], fz);
         fz = quad_sum(fz);
       }
     }
@@ -313,22 +325,29 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
         c[q] = b[q];
         if constexpr (PASS == 1) c[q] += 4 * q + l < Q ? coef[at(f, q)] : 0.0;
       }
-      if constexpr (PASS == 1) good = good && energy(b) <= kCorrTol * kCorrTol * energy(c);
-      if constexpr (SKIP == 0 && PASS == 1) {
+      double size = 0.0;
+      if constexpr (PASS == 1) size = energy(c);
+      if constexpr (SKIP == 0) {
         if (a.normals) {
           double fc = 0.0;
 #pragma unroll
           for (int d = 0; d < DIM; ++d)
-            fc += l == (1 + d) % 4 ? a.normals[(int64_t)t * DIM + d] * ie * c[(1 + d) / 4] : 0.0;
+            fc += l == (1 + d) % 4 ? fr[(1 + d) / 4] * c[(1 + d) / 4] : 0.0;
           fc = quad_sum(fc);
-          const double g = con ? fc / fz : 0.0;
+          double g = con ? fc / fz : 0.0;
           if (con) {
 #pragma unroll
             for (int q = 0; q < T::QB; ++q) c[q] = fma(-g, z[q], c[q]);
           }
+          if constexpr (PASS == 1) {
+            const double g0 = a.hweights[(int64_t)t * F + f];
+            size = fma(g0 * g0, energy(z), size);  // the eliminated part is of the solution's size too
+            g += g0;
+          }
           if (use && l == 0) a.hweights[(int64_t)t * F + f] = g;
         }
       }
+      if constexpr (PASS == 1) good = good && energy(b) <= kCorrTol * kCorrTol * size;
       if (use) {
 #pragma unroll
         for (int q = 0; q < T::QB; ++q)
@@ -336,8 +355,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
       }
     };
     int f = 0;
-    const int n = PASS == 0 ? Fp : F;
-    for (; f + 1 < n; f += 2) {
+    for (; f + 1 < F; f += 2) {
       double b[2][T::QB];
       rhs(f, b[0]);
       rhs(f + 1, b[1]);
@@ -345,7 +363,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
       finish(f, b[0]);
       finish(f + 1, b[1]);
     }
-    if (f < n) {
+    if (f < F) {
       double b[1][T::QB];
       rhs(f, b[0]);
       quad_solve<Q, 1>(M, b, l);
@@ -366,7 +384,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
   }
 }
 
-// R. sums [slot][Fp][Q]: P^T (W P c) of every right-hand side's coefficients,
+// R. sums [slot][F][Q]: P^T (W P c) of every right-hand side's coefficients,
 // a group of G lanes per target (rows as in the moment kernel: the same
 // scaled offsets and weights), the group's partial sums added through LDS in
 // lane order.  The rows are gathered once for all right-hand sides (LOOP, the
@@ -387,7 +405,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
   const int first = R.first, last = R.last, c0 = R.c0;
   const int lane = lane_id();
   const int grp = lane / G, lg = lane % G, grp0 = lane - lg;
-  const int Fp = a.F + (a.normals ? 1 : 0);
+  const int F = a.F;
   for (int i0 = first + xcd_block() * TPW; i0 < last; i0 += gridDim.x * TPW) {
     const int i = i0 + grp;
     const bool valid = i < last;
@@ -408,11 +426,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
       rows_sw<DIM>(xs, xt, rc.ie, a.p, [&](int r) { return lg + G * r < nrem; }, s, w);
     };
     if constexpr (!LOOP) load(0);
-    for (int f = 0; f < Fp; ++f) {
+    for (int f = 0; f < F; ++f) {
       double cf[QF], acc[QF];
       if constexpr (SKIP != 0) cf[0] = 0.0;
 #pragma unroll
-      for (int q = 0; q < Q; ++q) cf[q + SKIP] = coef[(loc * Fp + f) * Q + q];
+      for (int q = 0; q < Q; ++q) cf[q + SKIP] = coef[(loc * F + f) * Q + q];
 #pragma unroll
       for (int q = 0; q < QF; ++q) acc[q] = 0.0;
       for (int q0 = 0; q0 < cend; q0 += G * RPL) {
@@ -463,7 +481,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
             v += p.x;
             v += p.y;
           }
-          if (valid) sums[(loc * Fp + f) * Q + q] = v;
+          if (valid) sums[(loc * F + f) * Q + q] = v;
         }
       }
       __syncthreads();

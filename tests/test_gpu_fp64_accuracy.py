@@ -41,7 +41,7 @@ def own_rows(dim, n, side, mult, seed):
 CASES = [(b, d, o, n, side, mult) for b, d, o, n in
          [("scalar", 2, 2, 6), ("scalar", 2, 4, 15), ("scalar", 2, 4, 20), ("scalar", 3, 2, 12), ("scalar", 3, 3, 20),
           ("scalar", 3, 3, 24), ("scalar", 3, 3, 36), ("scalar", 3, 4, 37), ("scalar", 3, 4, 60), ("divfree", 3, 2, 13),
-          ("divfree", 3, 3, 26), ("staggered", 3, 3, 24)]
+          ("divfree", 3, 3, 26), ("staggered", 3, 3, 24), ("constrained", 3, 3, 24), ("constrained", 2, 4, 18)]
          for side, mult in [("full", 1.5), ("half", 1.5), ("half", 1.05)]]
 
 
