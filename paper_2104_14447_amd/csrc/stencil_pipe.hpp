@@ -676,6 +676,7 @@ __global__ __launch_bounds__(64) void k_pipe_weights(StencilArgs a, const PipeRe
             if (good && lg + G * r < nrem) run[lg + G * r] = v;
             if constexpr (SKIP != 0) rsum += lg + G * r < nrem ? v : 0.0;
           }
+          wave_lds_sync();  // cfs is rewritten for the next row
         } else {
 #pragma unroll
           for (int r = 0; r < RPL; ++r) {
