@@ -152,8 +152,10 @@ enum {
                                   A scheme not compiled for the shape makes gmls_stencils return
                                   GMLS_ERR_UNSUPPORTED.                                         */
   GMLS_OPT_PIPE_CHUNK = 5,     /* scheme 3: targets per pipeline chunk, 0 = all at once (0); the
-                                  workspace holds (moments + F*Q) doubles per chunk target; the
-                                  FP64 path's windows likewise, of at most 2^20 targets          */
+                                  workspace holds (moments + F*Q) doubles per chunk target.  The
+                                  FP64 pipeline (moments + 2*F*Q doubles) likewise, in windows of
+                                  at most 2^20 targets; below 4096 the FP64 call takes the QR
+                                  kernel, which needs no such workspace                          */
   GMLS_OPT_RADIUS_SCRATCH_MB = 6, /* radius search: device scratch (MiB) allowed for the one-pass
                                   search, 1 KiB per target; above it (or at 0) the search
                                   counts and fills in two passes (8192)                          */

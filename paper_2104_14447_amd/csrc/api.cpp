@@ -424,8 +424,11 @@ static hipError_t qr_left(gmls_ctx ctx, const Options &o, int dim, int order, in
 
 // Buffers of the FP64 pipeline for windows of at most kPipe64Chunk targets
 // (GMLS_OPT_PIPE_CHUNK where that is less); get: false where they cannot be
-// had (capture-safe: were not grown by an earlier call), the call then takes
-// the QR kernel, which needs none.
+// had (capture-safe: were not grown by an earlier call) or hold fewer than
+// kPipe64ChunkMin of the call's targets, which then takes the QR kernel, which
+// needs none.  Small windows are bound by their launches: 200k 3-D order-3
+// targets 520 us in one window, 810 in windows of 16384, 1870 of 4096, 6500 of
+// 1024, 2470 by QR.
 struct Fp64Pipe {
   double *mom = nullptr, *coef = nullptr, *sums = nullptr;
   void *rec = nullptr;
@@ -434,6 +437,7 @@ struct Fp64Pipe {
   bool get(gmls_ctx ctx, int dim, int order, size_t per_target, int n) {
     chunk = std::min<int64_t>(n, kPipe64Chunk);
     if (ctx->opt.pipe_chunk > 0) chunk = std::min(chunk, ctx->opt.pipe_chunk);
+    if (chunk < kPipe64ChunkMin) return false;
     const size_t cq = sizeof(double) * per_target * chunk;
     mom = (double *)ctx->ws(WS_PIPE_MOM, sizeof(double) * (size_t)pipe_num_moments(dim, order) * chunk);
     coef = (double *)ctx->ws(WS_PIPE_Y, cq);

@@ -254,10 +254,10 @@ hipError_t launch_fp64_wave_shared(int dim, int order, const Pipe64Set &ss, cons
 // the QR kernel on a bin's left targets (shape as in launch_qr_bin)
 hipError_t launch_qr_left(int dim, int order, int basis, int bin, int rpl, int wpe, const Pipe64Set &set, BinMeta *meta,
                           int n_blocks, hipStream_t s);
-// targets from which an FP64 call takes these, and the most of them the
-// pipeline's buffers hold at a time (at most 3.8 KB each)
+// targets from which an FP64 call takes these, and the most (at most 3.8 KB
+// each) and the fewest of them the pipeline's buffers hold at a time
 constexpr int kFp64FastMin = 12288;
-constexpr int64_t kPipe64Chunk = 1 << 20;
+constexpr int64_t kPipe64Chunk = 1 << 20, kPipe64ChunkMin = 4096;
 // one wavefront per target (bins launched as in launch_mixed_pipe)
 hipError_t launch_mixed_wave(int dim, int order, int basis, const StencilArgs &a, const int *list,
                              const BinMeta *hm, BinMeta *meta, int *fb, Stats *stats, const Options &opt, int n_max,
