@@ -631,7 +631,9 @@ __global__ __launch_bounds__(64) void k_pipe_weights(StencilArgs a, const PipeRe
   const int lane = lane_id();
   const int grp = lane / G, lg = lane % G;
   const int F = a.F;
-  const int ys = F * Q;  // coefficients of a target's plain monomials
+  // the coefficients of the plain monomials (constrained stencils keep one more
+  // solution per target)
+  const int ys = (F + (a.normals ? 1 : 0)) * Q;
   for (int i0 = first + xcd_block() * TPW; i0 < last; i0 += gridDim.x * TPW) {
     const int i = i0 + grp;
     const bool valid = i < last;

@@ -33,6 +33,8 @@
 // targets 2.2e-14 -> 1.2e-14).
 #pragma once
 
+#include <type_traits>
+
 #include "stencil_pipe.hpp"
 
 namespace gmls {
@@ -169,7 +171,7 @@ __device__ __forceinline__ void quad_solve(const double (&M)[QuadTri<Q>::N], dou
 // for three wavefronts per SIMD it spills and takes 2.6 times as long.
 //
 // PASS 0: the factor and c = M^-1 lambda' of every functional into coef
-// [slot][F][Q].  PASS 1: the same factor again (taking it once more costs less
+// [slot][F][Q] (CON: [F + 1], the constraint's solution last).  PASS 1: the same factor again (taking it once more costs less
 // than 1.7 KB per target through memory) and c += M^-1 (lambda' - sums).  The
 // constraint f . c = 0 of the Neumann stencils is eliminated in both: with
 // z = M^-1 f, g = f.c / f.z is the boundary weight and c -= g z (Section 2.3);
@@ -178,7 +180,7 @@ __device__ __forceinline__ void quad_solve(const double (&M)[QuadTri<Q>::N], dou
 // c and z bring their own errors to the difference: root mean square errors of
 // one-sided 3-D order-3 targets, 24 neighbours 9.5e-14 (QR 9.0e-14), 80
 // neighbours 3.9e-15 (5.8e-15); corrected together 5.7e-15 and 8.1e-16.
-template <int DIM, int ORDER, int SKIP, int PASS>
+template <int DIM, int ORDER, int SKIP, int PASS, bool CON>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_pipe_chol(
     StencilArgs a, PipeRec *rec, int win_lo, int win_hi, const double *mom, double *coef, const double *sums,
     int *left_list, int *left, BinMeta *meta) {
@@ -249,20 +251,18 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
       const uint64_t bad = __ballot(!ok);
       ok = ((bad >> (lane & ~3)) & 15u) == 0;
     }
-    // the sums over the quad of v_i^2 M_ii, entry 4 q + l on lane l
-    auto energy = [&](const double(&v)[T::QB]) {
-      double e = 0.0;
+    // M_ii of entry 4 q + l (0 in the padding)
+    auto mii = [&](int q) {
+      unsigned idx = 0;
 #pragma unroll
-      for (int q = 0; q < T::QB; ++q) {
-        unsigned idx = 0;
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (4 * q + u < Q) idx |= (unsigned)SI.idx[4 * q + u + SKIP][4 * q + u + SKIP] << (8 * u);
-        if (4 * q + 3 < Q || 4 * q + l < Q) e = fma(v[q] * v[q], mt[(idx >> (8 * l)) & 255u], e);
-      }
-      return quad_sum(e);
+      for (int u = 0; u < 4; ++u)
+        if (4 * q + u < Q) idx |= (unsigned)SI.idx[4 * q + u + SKIP][4 * q + u + SKIP] << (8 * u);
+      const double v = mt[(idx >> (8 * l)) & 255u];
+      return 4 * q + 3 < Q || 4 * q + l < Q ? v : 0.0;
     };
     bool good = true;  // PASS 1: every correction is small (kCorrTol)
+    // entry of the constraint's row on this lane, among the linear monomials
+    auto row = [&](int d) { return l == (1 + d) % 4 ? a.normals[(int64_t)t * DIM + d] * ie : 0.0; };
     // right-hand side f (PASS 1: its residual over the rows; the multiplier's
     // part is taken off on constrained stencils)
     auto rhs = [&](int f, double(&b)[T::QB]) {
@@ -281,73 +281,69 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
           if (i < Q) b[q] -= sums[(loc * F + f) * Q + i];
         }
       }
-      if constexpr (SKIP == 0 && PASS == 1) {
-        if (a.normals) {
-          const double g = a.hweights[(int64_t)t * F + f];
+      if constexpr (CON && PASS == 1) {
+        const double g = a.hweights[(int64_t)t * F + f];
 #pragma unroll
-          for (int d = 0; d < DIM; ++d)
-            b[(1 + d) / 4] -= l == (1 + d) % 4 ? g * (a.normals[(int64_t)t * DIM + d] * ie) : 0.0;
-        }
+        for (int d = 0; d < DIM; ++d)
+          b[(1 + d) / 4] -= g * row(d);
       }
     };
     // entry i of the solution of right-hand side f
-    auto at = [&](int f, int q) { return (loc * F + f) * Q + 4 * q + l; };
-    // the constraint (SKIP 0): its row fr, z = M^-1 fr and fr . z
-    double z[T::QB], fr[T::QB], fz = 0.0;
+    auto at = [&](int f, int q) { return (loc * (CON ? F + 1 : F) + f) * Q + 4 * q + l; };
+    // CON: z = M^-1 row (kept behind the functionals' coefficients, the registers
+    // being full) and row . z
+    double fz = 0.0;
     bool con = false;
-    if constexpr (SKIP == 0) {
-      if (a.normals) {
+    if constexpr (CON) {
+      if constexpr (PASS == 0) {
         double b[1][T::QB];
 #pragma unroll
-        for (int q = 0; q < T::QB; ++q) fr[q] = 0.0;
+        for (int q = 0; q < T::QB; ++q) b[0][q] = 0.0;
 #pragma unroll
-        for (int d = 0; d < DIM; ++d) {
-          const double v = a.normals[(int64_t)t * DIM + d];
-          con = con || v != 0.0;
-          fr[(1 + d) / 4] = l == (1 + d) % 4 ? v * ie : fr[(1 + d) / 4];
-        }
-#pragma unroll
-        for (int q = 0; q < T::QB; ++q) b[0][q] = fr[q];
+        for (int d = 0; d < DIM; ++d) b[0][(1 + d) / 4] += row(d);
         quad_solve<Q, 1>(M, b, l);
 #pragma unroll
-        for (int q = 0; q < T::QB; ++q) {
-          z[q] = 4 * q + l < Q ? b[0][q] : 0.0;
-          fz = fma(fr[q], z[q], fz);
-        }
-        fz = quad_sum(fz);
+        for (int q = 0; q < T::QB; ++q)
+          if (use && 4 * q + l < Q) coef[at(F, q)] = b[0][q];
       }
+#pragma unroll
+      for (int d = 0; d < DIM; ++d) {
+        con = con || a.normals[(int64_t)t * DIM + d] != 0.0;
+        fz += l == (1 + d) % 4 ? row(d) * coef[at(F, (1 + d) / 4)] : 0.0;
+      }
+      fz = quad_sum(fz);
     }
     auto finish = [&](int f, const double(&b)[T::QB]) {
 #pragma clang fp contract(off)
-      double c[T::QB];
+      double c[T::QB], excess = 0.0;  // the squared sizes of correction - bound, summed over the quad below
 #pragma unroll
       for (int q = 0; q < T::QB; ++q) {
         c[q] = b[q];
-        if constexpr (PASS == 1) c[q] += 4 * q + l < Q ? coef[at(f, q)] : 0.0;
-      }
-      double size = 0.0;
-      if constexpr (PASS == 1) size = energy(c);
-      if constexpr (SKIP == 0) {
-        if (a.normals) {
-          double fc = 0.0;
-#pragma unroll
-          for (int d = 0; d < DIM; ++d)
-            fc += l == (1 + d) % 4 ? fr[(1 + d) / 4] * c[(1 + d) / 4] : 0.0;
-          fc = quad_sum(fc);
-          double g = con ? fc / fz : 0.0;
-          if (con) {
-#pragma unroll
-            for (int q = 0; q < T::QB; ++q) c[q] = fma(-g, z[q], c[q]);
-          }
-          if constexpr (PASS == 1) {
-            const double g0 = a.hweights[(int64_t)t * F + f];
-            size = fma(g0 * g0, energy(z), size);  // the eliminated part is of the solution's size too
-            g += g0;
-          }
-          if (use && l == 0) a.hweights[(int64_t)t * F + f] = g;
+        if constexpr (PASS == 1) {
+          c[q] += 4 * q + l < Q ? coef[at(f, q)] : 0.0;
+          excess = fma(fma(-kCorrTol * kCorrTol * c[q], c[q], b[q] * b[q]), mii(q), excess);
         }
       }
-      if constexpr (PASS == 1) good = good && energy(b) <= kCorrTol * kCorrTol * size;
+      if constexpr (CON) {
+        double fc = 0.0;
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) fc += l == (1 + d) % 4 ? row(d) * c[(1 + d) / 4] : 0.0;
+        fc = quad_sum(fc);
+        double g = con ? fc / fz : 0.0;
+        const double g0 = PASS == 1 ? a.hweights[(int64_t)t * F + f] : 0.0;
+        if (con) {
+#pragma unroll
+          for (int q = 0; q < T::QB; ++q) {
+            const double z = 4 * q + l < Q ? coef[at(F, q)] : 0.0;
+            c[q] = fma(-g, z, c[q]);
+            // (the eliminated part is of the solution's size too)
+            if constexpr (PASS == 1) excess = fma(-kCorrTol * kCorrTol * g0 * g0 * z * z, mii(q), excess);
+          }
+        }
+        g += g0;
+        if (use && l == 0) a.hweights[(int64_t)t * F + f] = g;
+      }
+      if constexpr (PASS == 1) good = good && quad_sum(excess) <= 0.0;
       if (use) {
 #pragma unroll
         for (int q = 0; q < T::QB; ++q)
@@ -405,7 +401,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
   const int first = R.first, last = R.last, c0 = R.c0;
   const int lane = lane_id();
   const int grp = lane / G, lg = lane % G, grp0 = lane - lg;
-  const int F = a.F;
+  const int F = a.F, cs = (F + (a.normals ? 1 : 0)) * Q;  // coefficients of a target
   for (int i0 = first + xcd_block() * TPW; i0 < last; i0 += gridDim.x * TPW) {
     const int i = i0 + grp;
     const bool valid = i < last;
@@ -430,7 +426,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
       double cf[QF], acc[QF];
       if constexpr (SKIP != 0) cf[0] = 0.0;
 #pragma unroll
-      for (int q = 0; q < Q; ++q) cf[q + SKIP] = coef[(loc * F + f) * Q + q];
+      for (int q = 0; q < Q; ++q) cf[q + SKIP] = coef[loc * cs + f * Q + q];
 #pragma unroll
       for (int q = 0; q < QF; ++q) acc[q] = 0.0;
       for (int q0 = 0; q0 < cend; q0 += G * RPL) {
@@ -553,11 +549,21 @@ hipError_t launch_pipe64(const Pipe64Set *ss, const Pipe64Set *sv, const int *li
       int nbc = (n_win + 15) / 16;
       if (nbc > cus * 64) nbc = cus * 64;
       nbc = xcd_grid(nbc);
-      k_pipe_chol<DIM, ORDER, SKIP, 0>
-          <<<nbc, 64, 0, s>>>(ss->a, rec, win_lo, win_hi, mom, coef, sums, ss->left_list, ss->left, meta);
+      auto chol = [&](auto pass) {
+        constexpr int P = decltype(pass)::value;
+        if constexpr (SKIP == 0) {
+          if (ss->a.normals) {
+            k_pipe_chol<DIM, ORDER, 0, P, true>
+                <<<nbc, 64, 0, s>>>(ss->a, rec, win_lo, win_hi, mom, coef, sums, ss->left_list, ss->left, meta);
+            return;
+          }
+        }
+        k_pipe_chol<DIM, ORDER, SKIP, P, false>
+            <<<nbc, 64, 0, s>>>(ss->a, rec, win_lo, win_hi, mom, coef, sums, ss->left_list, ss->left, meta);
+      };
+      chol(std::integral_constant<int, 0>{});
       pipe64_bins<DIM, ORDER, SKIP, 0>(1, ss->a, rec, hm, meta, win_lo, win_hi, mom, coef, sums, cus, s);
-      k_pipe_chol<DIM, ORDER, SKIP, 1>
-          <<<nbc, 64, 0, s>>>(ss->a, rec, win_lo, win_hi, mom, coef, sums, ss->left_list, ss->left, meta);
+      chol(std::integral_constant<int, 1>{});
       pipe64_bins<DIM, ORDER, SKIP, 0>(2, ss->a, rec, hm, meta, win_lo, win_hi, mom, coef, sums, cus, s);
     }
     if constexpr (SKIP == 0 && has_pipe_div<DIM, ORDER>()) {
