@@ -365,7 +365,7 @@ gmls_status gmls_spmv(gmls_ctx ctx, int64_t n_rows, const int64_t *row_ptr, cons
  * forbid hipMalloc).  The same kernels and summation order as gmls_spmv, so
  * y is bit for bit the one gmls_spmv gives.  Its scratch (the list of rows
  * longer than 8192 entries) is a file-scope device array of the library of
- * 4 * (64 + 2^23 + 8064) bytes (32 MiB), one per GPU, held until the process ends;
+ * 4 * (192 + 2^23 + 512) bytes (32 MiB), one per GPU, held until the process ends;
  * its address on a device is looked up when a context is created there.
  *   n_rows  0 .. 8388608 (2^23); more returns GMLS_ERR_ARG and enqueues nothing
  * Other arguments as for gmls_spmv.  Every call on one GPU uses that GPU's

@@ -946,7 +946,7 @@ gmls_status gmls_spmv(gmls_ctx ctx, int64_t n_rows, const int64_t *row_ptr, cons
   DeviceGuard g(ctx->device);
   int *lr = (int *)ctx->ws(WS_SPMV_LONG, sizeof(int) * (size_t)kSpmvScratchWords(n_rows));
   if (!lr) return gmls_set_error(ctx, GMLS_ERR_NOMEM, "device workspace allocation failed");
-  GMLS_HIP(launch_spmv(n_rows, row_ptr, col, val, x, y, lr + 64, lr, (double *)(lr + kSpmvPartialWord(n_rows)), ctx->cus,
+  GMLS_HIP(launch_spmv(n_rows, row_ptr, col, val, x, y, lr + kSpmvListWord, lr, (double *)(lr + kSpmvPartialWord(n_rows)), ctx->cus,
                        ctx->stream));
   return GMLS_OK;
 }
@@ -963,9 +963,8 @@ gmls_status gmls_spmv_noalloc(gmls_ctx ctx, int64_t n_rows, const int64_t *row_p
   int *sp = spmv_scratch(ctx->device);
   if (!sp) return gmls_set_error(ctx, GMLS_ERR_HIP, "the scratch of gmls_spmv_noalloc was not set up on this device");
   DeviceGuard g(ctx->device);
-  // the counter at word 0 is cleared by a kernel of launch_spmv; the list
-  // starts at word 64
-  GMLS_HIP(launch_spmv(n_rows, row_ptr, col, val, x, y, sp + 64, sp, (double *)(sp + kSpmvPartialWord(kNoAllocSpmvRows)),
+  // the counters are cleared by a kernel of launch_spmv
+  GMLS_HIP(launch_spmv(n_rows, row_ptr, col, val, x, y, sp + kSpmvListWord, sp, (double *)(sp + kSpmvPartialWord(kNoAllocSpmvRows)),
                        ctx->cus, ctx->stream));
   return GMLS_OK;
 }

@@ -241,17 +241,21 @@ __global__ __launch_bounds__(256) void k_spmv(int64_t rows, const int64_t *rp, c
   }
 }
 
-// Rows handed on by k_spmv: up to kSpmvSplit of them in 64 segments each, a
-// block per segment, the block that finishes a row's last segment adding the
-// 64 sums in segment order; more than that, a block per row (enough blocks
-// without cutting).  done: a finished-segment counter per cut row, cleared
-// with n_long.
+// Rows handed on by k_spmv: up to kSpmvSplit of them in segments, as many (a
+// power of two, at most 64) as make no more than the grid's blocks, the block
+// that finishes a row's last segment adding the sums in segment order; more
+// rows than that, a block per row.  done: a finished-segment counter per cut
+// row, cleared with n_long.  63 rows of 20000 entries beside 200k short ones:
+// 193 us a product in 64 segments each (4032 of 312 entries, 16 to a block),
+// 93 in 4; 64 of 400000 680 uncut, 262 in 4.
 __global__ __launch_bounds__(256) void k_spmv_long(const int64_t *rp, const int32_t *col, const double *val,
                                                    const double *x, double *y, const int *long_rows,
                                                    const int *n_long, int *done, double *partial) {
   __shared__ double part[4];
   __shared__ int last;
-  const int n = *n_long, S = n <= kSpmvSplit ? 64 : 1;
+  const int n = *n_long;
+  int S = n <= kSpmvSplit ? 64 : 1;
+  while (n * S > kSpmvSegments && S > 1) S >>= 1;
   for (int64_t w = blockIdx.x; w < (int64_t)n * S; w += gridDim.x) {
     const int k = (int)(w / S);
     const int64_t r = long_rows[k], g = w % S;
@@ -272,8 +276,10 @@ __global__ __launch_bounds__(256) void k_spmv_long(const int64_t *rp, const int3
     }
     __syncthreads();
     if (last && threadIdx.x < 64) {
-      const double t = wave_sum_uniform(
-          __hip_atomic_load(partial + (int64_t)k * 64 + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+      const double seg = (int)threadIdx.x < S ? __hip_atomic_load(partial + (int64_t)k * S + threadIdx.x, __ATOMIC_RELAXED,
+                                                                  __HIP_MEMORY_SCOPE_AGENT)
+                                              : 0.0;
+      const double t = wave_sum_uniform(seg);
       if (threadIdx.x == 0) y[r] = t;
     }
     __syncthreads();
@@ -282,23 +288,21 @@ __global__ __launch_bounds__(256) void k_spmv_long(const int64_t *rp, const int3
 
 hipError_t launch_spmv(int64_t rows, const int64_t *rp, const int32_t *col, const double *val, const double *x,
                        double *y, int *long_rows, int *n_long, double *partial, int cus, hipStream_t s) {
-  static_assert(1 + kSpmvSplit <= 64, "the counters precede the list");
+  static_assert(1 + kSpmvSplit <= kSpmvListWord && 2 * kSpmvSplit <= kSpmvSegments, "scratch layout");
   hipError_t e = fill_zero(n_long, sizeof(int) * (1 + kSpmvSplit), s);
   if (e != hipSuccess) return e;
   int64_t g = (rows + 3) / 4;
   if (g > (1 << 22)) g = 1 << 22;
   g = xcd_grid((int)g);
   k_spmv<<<(unsigned)g, 256, 0, s>>>(rows, rp, col, val, x, y, long_rows, n_long);
-  k_spmv_long<<<256, 256, 0, s>>>(rp, col, val, x, y, long_rows, n_long, n_long + 1, partial);
+  k_spmv_long<<<kSpmvSegments, 256, 0, s>>>(rp, col, val, x, y, long_rows, n_long, n_long + 1, partial);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
-// Scratch of the allocation-free product (gmls_spmv_noalloc): the long-row
-// counter at word 0 and the long-row list from word 64 (256-byte aligned),
-// room for every row of a matrix of up to kNoAllocSpmvRows rows, then the
-// long rows' partial sums.  Each device
-// holds its own copy until the process ends; host code reaches it only
+// Scratch of the allocation-free product (gmls_spmv_noalloc), for every row of
+// a matrix of up to kNoAllocSpmvRows rows being long.  Each device holds its
+// own copy until the process ends; host code reaches it only
 // through the address hipGetSymbolAddress returns on that device.
 // ---------------------------------------------------------------------------
 static __device__ __align__(256) int scratch[kSpmvScratchWords(kNoAllocSpmvRows)];

@@ -347,11 +347,11 @@ hipError_t launch_spmv(int64_t rows, const int64_t *rp, const int32_t *col, cons
                        double *y, int *long_rows, int *n_long, double *partial, int cus, hipStream_t s);
 // scratch of a product of `rows` rows, in 4-byte words: the long-row counter
 // at word 0, finished-segment counters of up to kSpmvSplit long rows from
-// word 1, the long-row list from word 64, those rows' 64 partial sums after it
-constexpr int kSpmvSplit = 63;
-constexpr int kSpmvPartials = 64 * kSpmvSplit;
-constexpr int64_t kSpmvPartialWord(int64_t rows) { return 64 + ((rows + 1) & ~(int64_t)1); }
-constexpr int64_t kSpmvScratchWords(int64_t rows) { return kSpmvPartialWord(rows) + 2 * kSpmvPartials; }
+// word 1, the long-row list from word kSpmvListWord, the partial sums of up to
+// kSpmvSegments segments after it
+constexpr int kSpmvSplit = 128, kSpmvSegments = 256, kSpmvListWord = 192;
+constexpr int64_t kSpmvPartialWord(int64_t rows) { return kSpmvListWord + ((rows + 1) & ~(int64_t)1); }
+constexpr int64_t kSpmvScratchWords(int64_t rows) { return kSpmvPartialWord(rows) + 2 * kSpmvSegments; }
 // allocation-free product: rows of at most kNoAllocSpmvRows, the long-row
 // list in the file-scope device array of assemble.hip, whose address on a
 // device spmv_scratch_setup (called with that device current, once per
