@@ -433,7 +433,8 @@ struct Fp64Pipe {
   double *mom = nullptr, *coef = nullptr, *sums = nullptr;
   void *rec = nullptr;
   int64_t chunk = 0;
-  // per_target: right-hand sides times their length
+  // per_target: right-hand sides times their length (the constraint's solution
+  // is kept as one more)
   bool get(gmls_ctx ctx, int dim, int order, size_t per_target, int n) {
     chunk = std::min<int64_t>(n, kPipe64Chunk);
     if (ctx->opt.pipe_chunk > 0) chunk = std::min(chunk, ctx->opt.pipe_chunk);
@@ -564,7 +565,7 @@ static gmls_status run_stencils(gmls_ctx ctx, const double *coords, int64_t n_sr
   const bool pipe64 = fast && pipe64_supported(dim, order, basis) &&
                       p64.get(ctx, dim, order,
                               basis == GMLS_BASIS_DIVFREE ? (size_t)F * C * binom_l(order + dim, dim)
-                                                          : (size_t)F * Q,
+                                                          : (size_t)(F + (normals ? 1 : 0)) * Q,
                               n);
   const bool wave64 = fast && !normals && wave64_supported(dim, order, basis);
   const Pipe64Set set{a, fb, meta->left[0]};
