@@ -736,23 +736,38 @@ static gmls_status run_shared(gmls_ctx ctx, const double *coords, int64_t n_src,
     const bool ws = wave64_supported(dim, order, GMLS_BASIS_SCALAR);
     const bool pv = pipe64_supported(dim, order, GMLS_BASIS_DIVFREE);
     Fp64Pipe p64;
+    auto pipe = [&](const Pipe64Set *s0, const Pipe64Set *s1) {
+      return launch_fp64_pipe(dim, order, s0, s1, list, hb, meta, p64.mom, p64.coef, p64.sums, p64.rec, p64.chunk, n,
+                              ctx->cus, s);
+    };
+    bool long_v = false;  // the divergence-free set's long rows are still to be done
+    const size_t need_s = (size_t)Fs * qs, need_v = (size_t)Fv * dim * qs;
     if (ws) {
       GMLS_HIP(launch_fp64_wave_shared(dim, order, p_s, p_v, list, hb, meta, n, ctx->cus, s));
-    } else if (p64.get(ctx, dim, order, std::max((size_t)Fs, pv ? (size_t)Fv * dim : 0) * qs, n)) {
-      GMLS_HIP(launch_fp64_pipe(dim, order, &p_s, pv ? &p_v : nullptr, list, hb, meta, p64.mom, p64.coef, p64.sums,
-                                p64.rec, p64.chunk, n, ctx->cus, s));
-      if (!pv)
-        GMLS_HIP(launch_fp64_wave(dim, order, GMLS_BASIS_DIVFREE, p_v, list, hb, meta, n, ctx->cus, s));
+    } else if (pv && p64.get(ctx, dim, order, std::max(need_s, need_v), n)) {
+      GMLS_HIP(pipe(&p_s, &p_v));
     } else {
-      for (int b = 1; b < kNumBins; ++b)
+      // what there are buffers for, set by set, as the sets' own calls would
+      const bool qr_s = !p64.get(ctx, dim, order, need_s, n);
+      if (!qr_s) GMLS_HIP(pipe(&p_s, nullptr));
+      const bool qr_v = pv && !p64.get(ctx, dim, order, need_v, n);
+      if (pv && !qr_v) GMLS_HIP(pipe(nullptr, &p_v));
+      if (!pv) GMLS_HIP(launch_fp64_wave(dim, order, GMLS_BASIS_DIVFREE, p_v, list, hb, meta, n, ctx->cus, s));
+      // (the long rows of a divergence-free set of the wavefront kernel with them:
+      // the two calls of one bin would share its cursor)
+      for (int b = 1; b < kNumBins && (qr_s || qr_v); ++b) {
+        const bool both = qr_s && (qr_v || (!pv && b == kLongBin));
         if (!sync || hm.count[b] > 0)
-          GMLS_HIP(qr_bin(ctx, opt, dim, order, 0, b, sync ? hm.count[b] : n, as, &av, list, meta, s));
+          GMLS_HIP(qr_bin(ctx, opt, dim, order, qr_s ? GMLS_BASIS_SCALAR : GMLS_BASIS_DIVFREE, b,
+                          sync ? hm.count[b] : n, qr_s ? as : av, both ? &av : nullptr, list, meta, s));
+      }
+      long_v = !pv && !qr_s;
     }
     if (report) GMLS_HIP(hipEventRecord(ctx->ev[2], s));
     if (ws && (!sync || hm.count[kLongBin] > 0))
       GMLS_HIP(qr_bin(ctx, opt, dim, order, 0, kLongBin, sync ? hm.count[kLongBin] : n, as, &av, list, meta, s));
     GMLS_HIP(qr_left(ctx, opt, dim, order, GMLS_BASIS_SCALAR, p_s, list, hb, meta, n, false, s));
-    GMLS_HIP(qr_left(ctx, opt, dim, order, GMLS_BASIS_DIVFREE, p_v, list, hb, meta, n, !ws && !pv, s));
+    GMLS_HIP(qr_left(ctx, opt, dim, order, GMLS_BASIS_DIVFREE, p_v, list, hb, meta, n, long_v, s));
   } else if (scheme < 0) {
     for (int b = 1; b < kNumBins; ++b) {
       if (sync && hm.count[b] == 0) continue;
