@@ -324,7 +324,7 @@ hipError_t launch_binning(const int64_t *row_ptr, const double *targets, int n_t
                           size_t extra_bytes, hipStream_t s);
 hipError_t launch_rank_deficient(const StencilArgs &a, int C, const int *list, BinMeta *meta, hipStream_t s);
 // every target of `bin` to the FP64 fallback queue fb_list / *fb_count with
-// status FALLBACK (stats: counted there unless null)
+// status FALLBACK, counted in stats
 hipError_t launch_defer_bin(uint8_t *status, const int *list, const BinMeta *meta, int bin, int *fb_list,
                             int *fb_count, Stats *stats, hipStream_t s);
 

@@ -2,8 +2,8 @@
 // Compiled once per (GMLS_DIM, GMLS_ORDER, GMLS_BASIS) by the build, each
 // object defining launch_mixed_d<DIM>_o<ORDER>_b<BASIS> (the per-bin fused
 // kernels) and launch_pipe_d<DIM>_o<ORDER>_b<BASIS> (the three-kernel pipeline,
-// scalar bases with at most 20 functions); the scalar objects also define
-// launch_pipe64_d<DIM>_o<ORDER> (the FP64 pipeline).
+// scalar bases with at most 20 functions); the scalar objects of at most 20
+// functions also define launch_pipe64_d<DIM>_o<ORDER> (the FP64 pipeline).
 #include "stencil_mixed64.hpp"
 #include "stencil_pipe.hpp"
 #include "stencil_pipe64.hpp"
@@ -16,6 +16,9 @@
 #define GMLS_CAT(a, b, c, d, e, f) GMLS_CAT2(a, b, c, d, e, f)
 #define GMLS_FN GMLS_CAT(launch_mixed_d, GMLS_DIM, _o, GMLS_ORDER, _b, GMLS_BASIS)
 #define GMLS_PIPE_FN GMLS_CAT(launch_pipe_d, GMLS_DIM, _o, GMLS_ORDER, _b, GMLS_BASIS)
+// monomials of degree <= order: binomial(order + dim, dim)
+#define GMLS_NUM_MONO \
+  (GMLS_DIM == 2 ? (GMLS_ORDER + 1) * (GMLS_ORDER + 2) / 2 : (GMLS_ORDER + 1) * (GMLS_ORDER + 2) * (GMLS_ORDER + 3) / 6)
 #define GMLS_PIPE64_FN GMLS_CAT(launch_pipe64_d, GMLS_DIM, _o, GMLS_ORDER, , )
 
 namespace gmls {
@@ -71,19 +74,16 @@ hipError_t GMLS_PIPE_FN(const StencilArgs &a, const int *list, const BinMeta *hm
   }
 }
 
-#if GMLS_BASIS == 0
+#if GMLS_BASIS == 0 && GMLS_NUM_MONO <= 20
 hipError_t GMLS_PIPE64_FN(const Pipe64Set *ss, const Pipe64Set *sv, const int *list, const BinMeta *hm, BinMeta *meta,
                           double *mom, double *coef, double *sums, void *rec, int64_t chunk, int n_max, int cus,
                           hipStream_t s) {
   constexpr int D = GMLS_DIM, O = GMLS_ORDER;
   PipeRec *r = (PipeRec *)rec;
-  if constexpr (has_pipe<D, O>()) {
-    if (ss && ss->a.skip_const)  // staggered stencils
-      return launch_pipe64<D, O, 1>(ss, sv, list, hm, meta, mom, coef, sums, r, chunk, n_max, cus, s);
-    return launch_pipe64<D, O, 0>(ss, sv, list, hm, meta, mom, coef, sums, r, chunk, n_max, cus, s);
-  } else {
-    return hipErrorInvalidValue;
-  }
+  static_assert(has_pipe<D, O>() && num_mono(D, O) == GMLS_NUM_MONO, "");
+  if (ss && ss->a.skip_const)  // staggered stencils
+    return launch_pipe64<D, O, 1>(ss, sv, list, hm, meta, mom, coef, sums, r, chunk, n_max, cus, s);
+  return launch_pipe64<D, O, 0>(ss, sv, list, hm, meta, mom, coef, sums, r, chunk, n_max, cus, s);
 }
 #endif
 

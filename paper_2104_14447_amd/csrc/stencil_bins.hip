@@ -320,7 +320,7 @@ __global__ void k_rank_deficient(StencilArgs a, int C, const int *list, const Bi
 }
 
 // The targets of bin `bin` handed to the FP64 QR kernels: status FALLBACK,
-// queued on fb_list (counter *fb_count), counted in stats (may be null).
+// queued on fb_list (counter *fb_count), counted in stats.
 // The wavefront and fused mixed kernels hold a row's sample in registers and
 // take the long bin this way; the QR kernels factor long rows in chunks.
 __global__ void k_defer_bin(uint8_t *status, const int *list, const BinMeta *meta, int bin, int *fb_list,
@@ -331,7 +331,7 @@ __global__ void k_defer_bin(uint8_t *status, const int *list, const BinMeta *met
     status[t] = GMLS_TARGET_FALLBACK;
     fb_list[atomicAdd(fb_count, 1)] = t;
   }
-  if (stats && blockIdx.x == 0 && threadIdx.x == 0 && n > 0) atomicAdd(&stats->n_fallback, (unsigned long long)n);
+  if (blockIdx.x == 0 && threadIdx.x == 0 && n > 0) atomicAdd(&stats->n_fallback, (unsigned long long)n);
 }
 
 hipError_t launch_defer_bin(uint8_t *status, const int *list, const BinMeta *meta, int bin, int *fb_list,

@@ -93,13 +93,11 @@ hipError_t launch_pipe64_d3_o2(const Pipe64Set *, const Pipe64Set *, const int *
                                double *, double *, void *, int64_t, int, int, hipStream_t);
 hipError_t launch_pipe64_d3_o3(const Pipe64Set *, const Pipe64Set *, const int *, const BinMeta *, BinMeta *, double *,
                                double *, double *, void *, int64_t, int, int, hipStream_t);
-hipError_t launch_pipe64_d3_o4(const Pipe64Set *, const Pipe64Set *, const int *, const BinMeta *, BinMeta *, double *,
-                               double *, double *, void *, int64_t, int, int, hipStream_t);
 using Pipe64Fn = hipError_t (*)(const Pipe64Set *, const Pipe64Set *, const int *, const BinMeta *, BinMeta *, double *,
                                 double *, double *, void *, int64_t, int, int, hipStream_t);
 static const Pipe64Fn kPipe64[2][4] = {
     {launch_pipe64_d2_o1, launch_pipe64_d2_o2, launch_pipe64_d2_o3, launch_pipe64_d2_o4},
-    {launch_pipe64_d3_o1, launch_pipe64_d3_o2, launch_pipe64_d3_o3, launch_pipe64_d3_o4}};
+    {launch_pipe64_d3_o1, launch_pipe64_d3_o2, launch_pipe64_d3_o3, nullptr}};  // order 4: the wavefront kernel
 
 hipError_t launch_wave_d2_o1_b0(const StencilArgs &, const int *, const BinMeta *, BinMeta *, int *, Stats *,
                                 const Options &, int, int, PipeTimer *, hipStream_t);
@@ -170,47 +168,17 @@ static const SharedFn kShared[2][4] = {
     {launch_wave_shared_d2_o1, launch_wave_shared_d2_o2, launch_wave_shared_d2_o3, launch_wave_shared_d2_o4},
     {launch_wave_shared_d3_o1, launch_wave_shared_d3_o2, launch_wave_shared_d3_o3, launch_wave_shared_d3_o4}};
 
-hipError_t launch_wave64_d2_o1_b0(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
-hipError_t launch_wave64_d2_o1_b1(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
-hipError_t launch_wave64_shared_d2_o1(const Pipe64Set &, const Pipe64Set &, const int *, const BinMeta *, BinMeta *,
-                                     int, int, hipStream_t);
-hipError_t launch_wave64_d2_o2_b0(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
-hipError_t launch_wave64_d2_o2_b1(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
-hipError_t launch_wave64_shared_d2_o2(const Pipe64Set &, const Pipe64Set &, const int *, const BinMeta *, BinMeta *,
-                                     int, int, hipStream_t);
-hipError_t launch_wave64_d2_o3_b0(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
-hipError_t launch_wave64_d2_o3_b1(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
-hipError_t launch_wave64_shared_d2_o3(const Pipe64Set &, const Pipe64Set &, const int *, const BinMeta *, BinMeta *,
-                                     int, int, hipStream_t);
-hipError_t launch_wave64_d2_o4_b0(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
 hipError_t launch_wave64_d2_o4_b1(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
-hipError_t launch_wave64_shared_d2_o4(const Pipe64Set &, const Pipe64Set &, const int *, const BinMeta *, BinMeta *,
-                                     int, int, hipStream_t);
-hipError_t launch_wave64_d3_o1_b0(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
-hipError_t launch_wave64_d3_o1_b1(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
-hipError_t launch_wave64_shared_d3_o1(const Pipe64Set &, const Pipe64Set &, const int *, const BinMeta *, BinMeta *,
-                                     int, int, hipStream_t);
-hipError_t launch_wave64_d3_o2_b0(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
-hipError_t launch_wave64_d3_o2_b1(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
-hipError_t launch_wave64_shared_d3_o2(const Pipe64Set &, const Pipe64Set &, const int *, const BinMeta *, BinMeta *,
-                                     int, int, hipStream_t);
-hipError_t launch_wave64_d3_o3_b0(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
 hipError_t launch_wave64_d3_o3_b1(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
-hipError_t launch_wave64_shared_d3_o3(const Pipe64Set &, const Pipe64Set &, const int *, const BinMeta *, BinMeta *,
-                                     int, int, hipStream_t);
 hipError_t launch_wave64_d3_o4_b0(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
 hipError_t launch_wave64_d3_o4_b1(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
 hipError_t launch_wave64_shared_d3_o4(const Pipe64Set &, const Pipe64Set &, const int *, const BinMeta *, BinMeta *,
                                      int, int, hipStream_t);
 using Wave64Fn = hipError_t (*)(const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int, hipStream_t);
+// null: the pipeline's
 static const Wave64Fn kWave64[2][4][2] = {
-    {{launch_wave64_d2_o1_b0, launch_wave64_d2_o1_b1}, {launch_wave64_d2_o2_b0, launch_wave64_d2_o2_b1}, {launch_wave64_d2_o3_b0, launch_wave64_d2_o3_b1}, {launch_wave64_d2_o4_b0, launch_wave64_d2_o4_b1}},
-    {{launch_wave64_d3_o1_b0, launch_wave64_d3_o1_b1}, {launch_wave64_d3_o2_b0, launch_wave64_d3_o2_b1}, {launch_wave64_d3_o3_b0, launch_wave64_d3_o3_b1}, {launch_wave64_d3_o4_b0, launch_wave64_d3_o4_b1}}};
-using Shared64Fn = hipError_t (*)(const Pipe64Set &, const Pipe64Set &, const int *, const BinMeta *, BinMeta *, int, int,
-                                  hipStream_t);
-static const Shared64Fn kShared64[2][4] = {
-    {launch_wave64_shared_d2_o1, launch_wave64_shared_d2_o2, launch_wave64_shared_d2_o3, launch_wave64_shared_d2_o4},
-    {launch_wave64_shared_d3_o1, launch_wave64_shared_d3_o2, launch_wave64_shared_d3_o3, launch_wave64_shared_d3_o4}};
+    {{}, {}, {}, {nullptr, launch_wave64_d2_o4_b1}},
+    {{}, {}, {nullptr, launch_wave64_d3_o3_b1}, {launch_wave64_d3_o4_b0, launch_wave64_d3_o4_b1}}};
 
 using MixedFn = hipError_t (*)(int, const StencilArgs &, const int *, BinMeta *, int *, Stats *, const Options &, int,
                                int, hipStream_t);
@@ -292,8 +260,8 @@ hipError_t launch_fp64_wave(int dim, int order, int basis, const Pipe64Set &set,
 
 hipError_t launch_fp64_wave_shared(int dim, int order, const Pipe64Set &ss, const Pipe64Set &sv, const int *list,
                                    const BinMeta *hm, BinMeta *meta, int n_max, int cus, hipStream_t s) {
-  if (!wave64_supported(dim, order, 0)) return hipErrorInvalidValue;
-  return kShared64[dim - 2][order - 1](ss, sv, list, hm, meta, n_max, cus, s);
+  if (!wave64_supported(dim, order, 0)) return hipErrorInvalidValue;  // order 4 in 3-D alone
+  return launch_wave64_shared_d3_o4(ss, sv, list, hm, meta, n_max, cus, s);
 }
 
 hipError_t launch_mixed_bin(int dim, int order, int basis, int bin, const StencilArgs &a, const int *list,

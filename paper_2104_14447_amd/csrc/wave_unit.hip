@@ -18,6 +18,9 @@
 
 #define GMLS_CAT2(a, b, c, d, e, f) a##b##c##d##e##f
 #define GMLS_CAT(a, b, c, d, e, f) GMLS_CAT2(a, b, c, d, e, f)
+// monomials of degree <= order: binomial(order + dim, dim)
+#define GMLS_NUM_MONO \
+  (GMLS_DIM == 2 ? (GMLS_ORDER + 1) * (GMLS_ORDER + 2) / 2 : (GMLS_ORDER + 1) * (GMLS_ORDER + 2) * (GMLS_ORDER + 3) / 6)
 #define GMLS_WAVE_FN GMLS_CAT(launch_wave_d, GMLS_DIM, _o, GMLS_ORDER, _b, GMLS_BASIS)
 #define GMLS_SHARED_FN GMLS_CAT(launch_wave_shared_d, GMLS_DIM, _o, GMLS_ORDER, , )
 #define GMLS_WAVE64_FN GMLS_CAT(launch_wave64_d, GMLS_DIM, _o, GMLS_ORDER, _b, GMLS_BASIS)
@@ -32,14 +35,14 @@ hipError_t GMLS_WAVE_FN(const StencilArgs &a, const int *list, const BinMeta *hm
   return launch_wave<GMLS_DIM, GMLS_ORDER, GMLS_BASIS>(one, one, list, hm, meta, stats, opt, n_max, cus, timer, s);
 }
 
+#if GMLS_NUM_MONO > (GMLS_BASIS == 1 ? 10 : 20)
 hipError_t GMLS_WAVE64_FN(const Pipe64Set &set, const int *list, const BinMeta *hm, BinMeta *meta, int n_max, int cus,
                           hipStream_t s) {
   const WaveSet one{set.a, set.left_list, set.left};
-  if constexpr (GMLS_BASIS == 1 ? !has_pipe_div<GMLS_DIM, GMLS_ORDER>() : !has_pipe<GMLS_DIM, GMLS_ORDER>())
-    return launch_wave64<GMLS_DIM, GMLS_ORDER, GMLS_BASIS>(one, one, list, hm, meta, n_max, cus, s);
-  else
-    return hipErrorInvalidValue;
+  static_assert(GMLS_BASIS == 1 ? !has_pipe_div<GMLS_DIM, GMLS_ORDER>() : !has_pipe<GMLS_DIM, GMLS_ORDER>(), "");
+  return launch_wave64<GMLS_DIM, GMLS_ORDER, GMLS_BASIS>(one, one, list, hm, meta, n_max, cus, s);
 }
+#endif
 #endif
 
 #if GMLS_BASIS == 1 && GMLS_PART != 0
@@ -51,14 +54,14 @@ hipError_t GMLS_SHARED_FN(const StencilArgs &as, int *fbs, int *fbs_count, const
   return launch_wave<GMLS_DIM, GMLS_ORDER, 3>(ss, sv, list, hm, meta, stats, opt, n_max, cus, timer, s);
 }
 
+#if GMLS_NUM_MONO > 20
 hipError_t GMLS_SHARED64_FN(const Pipe64Set &s0, const Pipe64Set &s1, const int *list, const BinMeta *hm, BinMeta *meta,
                             int n_max, int cus, hipStream_t s) {
   const WaveSet ss{s0.a, s0.left_list, s0.left}, sv{s1.a, s1.left_list, s1.left};
-  if constexpr (!has_pipe<GMLS_DIM, GMLS_ORDER>())
-    return launch_wave64<GMLS_DIM, GMLS_ORDER, 3>(ss, sv, list, hm, meta, n_max, cus, s);
-  else
-    return hipErrorInvalidValue;
+  static_assert(!has_pipe<GMLS_DIM, GMLS_ORDER>(), "");
+  return launch_wave64<GMLS_DIM, GMLS_ORDER, 3>(ss, sv, list, hm, meta, n_max, cus, s);
 }
+#endif
 #endif
 
 }  // namespace gmls
