@@ -180,17 +180,21 @@ enum {
                                        nothing was tuned, the library's default for the basis,
                                        kernel and bin;
                                   0, 1, 2 = this candidate in every bin (gmls_tune_result lists
-                                       the lanes per target and rows per lane of each).          */
+                                       the lanes per target and rows per lane of each).
+                                  The mixed pipeline's; the FP64 one keeps the defaults.         */
   GMLS_OPT_SOURCE_STRIDE = 10, /* layout of `coords` in the stencil calls (gmls_stencils, _multi,
                                   _constrained, _staggered) (0): source j is at coords[j*stride ..
                                   j*stride + dim); 0 means stride = dim; otherwise an integer in
                                   [dim, 64].  Use 4 with the records of gmls_neighbors_sorted.
                                   The search calls always read [n][dim].                         */
   GMLS_OPT_WAVE_SHAPE = 11,    /* variant of the wavefront kernel (mixed scheme 4) (-1): -1 the
-                                  autotuned choice per bin, else this candidate in every bin      */
+                                  autotuned choice per bin, else this candidate in every bin;
+                                  the wavefront kernel of FP64 calls keeps its default            */
   GMLS_OPT_QR_SHAPE = 12       /* shape of the FP64 QR kernel per bin (-1): -1 the autotuned
                                   choice, else this candidate in every bin (gmls_tune_result),
-                                  the QR kernel then taking every FP64 call whatever its size    */
+                                  the QR kernel then taking every FP64 call whatever its size;
+                                  with -1, calls of 12288 targets and more use it (in the tuned
+                                  shapes) only for the targets that their own kernels leave to it */
 };
 
 /* Create a context on HIP device `device`, enqueuing on `hip_stream`
@@ -473,7 +477,10 @@ gmls_status gmls_stencils_multi(gmls_ctx ctx, const double *coords, int64_t n_sr
  * the smallest time (minimum over the repetitions) in the context's table,
  * keyed by (dim, order, basis); later calls with that key use it unless
  * GMLS_OPT_PIPE_SHAPE, GMLS_OPT_WAVE_SHAPE or GMLS_OPT_QR_SHAPE force a
- * candidate.  Bins without targets keep their previous entry.
+ * candidate.  Bins without targets keep their previous entry.  FP64 calls of
+ * 12288 targets and more mostly run other kernels (GMLS_PREC_FP64), which have
+ * one shape per bin: for them kernel 3 is timed all the same, on the whole
+ * call, and its choice serves the targets left to QR and smaller calls.
  *   basis     GMLS_BASIS_SCALAR, GMLS_BASIS_DIVFREE, or GMLS_TUNE_SHARED: the
  *             kernels that gmls_stencils_multi runs for a scalar and a
  *             divergence-free set of one order on the same rows (kernels 2
