@@ -163,16 +163,18 @@ __device__ __forceinline__ void quad_solve(const double (&M)[QuadTri<Q>::N], dou
 }
 
 // B. Four lanes per target: the factor of 20 monomials is 60 doubles a lane,
-// so that it stays in registers at two wavefronts per SIMD (one thread per
-// target needs 210 and spills; a wavefront per target idles 44 lanes), and
+// which two wavefronts per SIMD hold but for 4 and 12 spilled registers of the
+// two passes (constrained: 11 and 32; one thread per target needs 210 doubles;
+// a wavefront per target idles 44 lanes), and
 // pivots and columns pass between the lanes by DPP.  Bound by instruction
 // issue: a third are those moves (2 per double).  0.33 ms per million targets
 // and pass at order 3 and one right-hand side, 0.12 ms for each more; compiled
 // for three wavefronts per SIMD it spills and takes 2.6 times as long.
 //
 // PASS 0: the factor and c = M^-1 lambda' of every functional into coef
-// [slot][F][Q] (CON: [F + 1], the constraint's solution last).  PASS 1: the same factor again (taking it once more costs less
-// than 1.7 KB per target through memory) and c += M^-1 (lambda' - sums).  The
+// [slot][F][Q] (CON: [F + 1], the constraint's solution last).  PASS 1: the
+// same factor again (taking it once more costs less than 1.7 KB per target
+// through memory) and c += M^-1 (lambda' - sums).  The
 // constraint f . c = 0 of the Neumann stencils is eliminated in both: with
 // z = M^-1 f, g = f.c / f.z is the boundary weight and c -= g z (Section 2.3);
 // PASS 1 corrects c and g together, from the residual lambda' - sums - g f, and
