@@ -387,15 +387,19 @@ static hipError_t qr_bin(gmls_ctx ctx, const Options &o, int dim, int order, int
 
 // Whether an FP64 call of n targets takes the kernels that solve with the
 // moment Gram and correct over the rows, not QR targets: it has targets enough
-// and the QR kernel's shape is neither forced nor being tuned.  The line is
-// where the fewer, longer launches of QR stop being faster (scalar bases, kNN
-// rows, whole step): 3-D order 3 at 1000 / 3000 / 6000 / 12000 targets 274 /
-// 329 / 405 / 498 us by QR and 300 / 312 / 344 / 379 us by the pipeline, 2-D
-// order 2 203 / 262 / 299 / 370 and 230 / 249 / 238 / 246 us, the others
-// between; and later for a scalar and a divergence-free set together, whose
-// QR kernel shares its factor (9000 targets, 3-D order 2 / 2-D order 4: 494 /
-// 478 us by QR, 507 / 494 us); one line for all, so that a set's weights do
-// not depend on the call it came with.
+// and the QR kernel's shape is neither forced nor being tuned.  One line for
+// all calls, so that a set's weights do not depend on the call it came with,
+// above the last shape to gain: two bases whose QR kernel shares its factor.
+// Whole step (kNN rows), us by QR / by the other kernels:
+//   targets               3000       6000       9000       12000
+//   2-D order 2        153 / 167  226 / 179  265 / 182  302 / 184
+//   3-D order 3        187 / 195  254 / 211  313 / 236  354 / 243
+//   3-D order 4        286 / 210  430 / 278  554 / 323  674 / 344
+//   constrained 3-D 3  195 / 198  265 / 216  321 / 242  356 / 252
+//   two, 3-D order 2   208 / 303  290 / 330  335 / 351  378 / 363
+//   two, 2-D order 4   234 / 263  309 / 327  370 / 383  442 / 392
+// A line at 6000 would be 1.2 to 1.7 times faster for one basis below 12288
+// and up to 1.14 times slower for two.
 static bool fp64_fast(gmls_ctx ctx, int n) { return n >= kFp64FastMin && ctx->opt.qr_force < 0 && !ctx->timer; }
 
 // The QR kernel, in each bin's shape, on what the FP64 kernels of many targets

@@ -180,8 +180,8 @@ hipError_t launch_stokes_assembly(const StokesArgs &s, int64_t *rlen, int64_t *a
 // dispatcher, where a grid of 64 blocks per CU walked the rows (996 -> 850
 // us), in contiguous ranges per XCD (-> 826 us); loads that bypass the caches
 // gain 2 % more there and lose a quarter on a matrix that the last-level
-// cache holds (55 -> 72 us at 20M entries).  Long rows over up to 64 blocks
-// (one block took 240 us for the multiplier row).  The 281M-entry Stokes
+// cache holds (55 -> 72 us at 20M entries).  Long rows are cut over up
+// to 64 blocks each (one block took 240 us for the multiplier row).  The 281M-entry Stokes
 // operator of 287k particles: 1172 -> 826 us, 2.9 -> 4.1 TB/s.
 // ---------------------------------------------------------------------------
 constexpr int kLongRow = 8192;
