@@ -511,14 +511,23 @@ def gmls_assemble_stokes(ctx: Context, row_ptr: torch.Tensor, col: torch.Tensor,
     cap = (dim * (dim + 1) + 1) * col.numel() + (dim + 2) * n
     nnz = ctypes.c_int64()
     L = load_library()
-    for _ in range(2):
-        a_col = torch.empty(max(cap, 1), dtype=torch.int32, device=dev)
-        a_val = torch.empty(max(cap, 1), dtype=torch.float64, device=dev)
+
+    def entries(m):
+        return (torch.empty(max(m, 1), dtype=torch.int32, device=dev),
+                torch.empty(max(m, 1), dtype=torch.float64, device=dev))
+
+    try:
+        a_col, a_val = entries(cap)
+    except torch.OutOfMemoryError:  # a cloud of many boundary particles needs less: ask how much
+        cap = 0
+        a_col, a_val = entries(cap)
+    for again in (True, False):
         rc = L.gmls_assemble_stokes(ctx._h, ctypes.byref(st), float(nu), _ptr(a_rp), _ptr(a_col), _ptr(a_val), cap,
                                     ctypes.byref(nnz))
-        if rc != GMLS_ERR_CAPACITY:
+        if rc != GMLS_ERR_CAPACITY or not again:
             break
         cap = nnz.value
+        a_col, a_val = entries(cap)
     if rc != GMLS_OK:
         ctx._raise(rc)
     return a_rp, a_col[: nnz.value], a_val[: nnz.value]
